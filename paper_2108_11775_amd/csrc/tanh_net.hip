@@ -44,13 +44,14 @@ __device__ __forceinline__ void tanh_slope(float z, float &a, float &d) {
 }
 
 // The same from a pre-activation held scaled by 2^zs, k = -2 log2(e) 2^-zs, returning
-// as tanh (as a power of two) and a quarter of the slope, d4: all scalings are exact, so
-// a / as and 4 d4 are the bits tanh_slope gives for z 2^-zs, in nine instructions.
-__device__ __forceinline__ void tanh_slope_sc(float z, float k, float as, float &a, float &d4) {
+// as tanh (as a power of two): with r2 = 2/(1 + e) the factors 2 and 4 are taken before the
+// rounding, by exact scalings, so a / as and d are the bits tanh_slope gives for z 2^-zs, in
+// nine instructions.
+__device__ __forceinline__ void tanh_slope_sc(float z, float k, float as, float &a, float &d) {
     const float e = exp2_fast(k * fabsf(z));
-    const float r = __builtin_amdgcn_rcpf(1.0f + e);
-    a = copysignf(fmaf(-e, as, as) * r, z);
-    d4 = e * (r * r);
+    const float r2 = __builtin_amdgcn_rcpf(fmaf(e, 0.5f, 0.5f));
+    a = copysignf(fmaf(-e, 0.5f * as, 0.5f * as) * r2, z);
+    d = e * (r2 * r2);
 }
 
 // Offset of W_l in the flat parameter vector (l = L gives v).
@@ -202,7 +203,7 @@ struct TnLdsX6 {
     bf16x8_t bw[NF > 0 ? NF : 1];
     float w0t[DIM][HP];  // W_0 transposed
     float bias[L][HP];
-    float vo[HP], vd[HP];  // v and 4^L v: the reverse pass takes quarters of the slopes
+    float vo[HP];
     float bo;
     TnFwd F;  // the forward products' scheme
 };
@@ -258,7 +259,6 @@ __device__ void tn_stage_x6(TnLdsX6<DIM, NT, L> &S, const float *__restrict__ P,
             S.bias[l][idx] = fh && l > 0 ? ldexpf(b, S.F.fsw[l - 1] + kTnAct) : b;
         }
         S.vo[idx] = ok ? P[tn_w_off(L, DIM, H) + idx] : 0.0f;
-        S.vd[idx] = ldexpf(S.vo[idx], 2 * L);
     }
     if (threadIdx.x == 0) S.bo = P[tn_w_off(L, DIM, H) + H];
 }
@@ -380,12 +380,11 @@ __device__ __forceinline__ void tn_point_x6(const TnLdsX6<DIM, NT, L> &S, const 
     }
     s = tn_sum4(p) + S.bo;
     if (!GRAD) return;
-    // reverse order: e_L = v * d_L, e_l = d_l * (W_l^T e_{l+1}), grad s = W_0^T e_1,
-    // 4^(l-1) e_l at hand (quarter slopes from 4^L v: exact, and e_1 itself at the end)
+    // reverse order: e_L = v * d_L, e_l = d_l * (W_l^T e_{l+1}), grad s = W_0^T e_1
     f32x4_tn e[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const float4 vv = tn_ld4(&S.vd[16 * t + u4]);
+        const float4 vv = tn_ld4(&S.vo[16 * t + u4]);
         e[t][0] = vv.x * d[L - 1][t][0];
         e[t][1] = vv.y * d[L - 1][t][1];
         e[t][2] = vv.z * d[L - 1][t][2];
@@ -600,7 +599,7 @@ __device__ __forceinline__ void tn_small_body(TnSmallLds<DIM, NT, L> &S,
     constexpr bool GRAD = MODE != kEval;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, u4 = 4 * (lane >> 4);
     uint4 fw[LH][KB][FP], bw[GRAD ? LH : 1][KB][3];
-    float bias[L][4], vd[4], kz[L];
+    float bias[L][4], kz[L];
 #pragma unroll
     for (int l = 1; l < L; ++l)
 #pragma unroll
@@ -632,9 +631,6 @@ __device__ __forceinline__ void tn_small_body(TnSmallLds<DIM, NT, L> &S,
         for (int v = 0; v < 4; ++v) bias[l][v] = ldexpf(R.bias[l][v], sc);
         kz[l] = ldexpf(-2.0f * kLog2e, -sc);
     }
-    // the reverse pass takes quarters of the slopes: 4^L v
-#pragma unroll
-    for (int v = 0; v < 4; ++v) vd[v] = ldexpf(R.v[v], 2 * L);
 
     int buf = 0;
     // all tiles' values of the lane's units, FP32
@@ -733,10 +729,10 @@ __device__ __forceinline__ void tn_small_body(TnSmallLds<DIM, NT, L> &S,
             }
             s = tn_sum4(p) + R.bo;
             if constexpr (GRAD) {
-                // 4^(l-1) e_l: e_L = v d_L, e_l = d_l (W_l^T e_{l+1}), grad s = W_0^T e_1
+                // e_L = v d_L, e_l = d_l (W_l^T e_{l+1}), grad s = W_0^T e_1
                 float e[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) e[v] = vd[v] * d[L - 1][v];
+                for (int v = 0; v < 4; ++v) e[v] = R.v[v] * d[L - 1][v];
 #pragma unroll
                 for (int l = L - 1; l >= 1; --l) {
                     const f32x4_tn zero = {};

@@ -367,3 +367,34 @@ def test_small_batches_give_the_large_batch_s_bits(dim, H, L, n, fp16):
     for f in (P.tanh_occupancy_eval, P.tanh_occupancy_grad):
         for a, b in zip(f(net, xs), f(net, x)):
             assert torch.equal(a, b[..., :n])
+
+
+# both kernels (few and many points), every depth
+@pytest.mark.parametrize("n", [100, 20000])
+@pytest.mark.parametrize("dim,H,L", [(2, 64, 1), (3, 33, 2), (2, 16, 3), (3, 64, 4)])
+def test_output_weights_near_the_top_of_the_range(dim, H, L, n):
+    """Output weights of 2^125 to 2^127 times a W_0 of 2^-112 (activations 0, slopes 1): the
+    gradient is that of 2^-127 times the weights, scaled, and 0 where sigma' is."""
+    require_gpu()
+    import torch
+    rng = np.random.default_rng(L)
+    p = rng.uniform(0.3, 0.9, O.tanh_nparams(dim, H, L)).astype(np.float32)
+    w0 = H * dim + H
+    p[:w0] *= np.float32(2.0 ** -112)
+    for l in range(1, L):
+        hid = p[w0 + (l - 1) * (H * H + H):][:H * H + H]
+        hid[:H * H] /= H
+        hid[H * H:] = 0
+    p[-1] = 0.125
+    big = p.copy()
+    big[-1 - H:-1] *= np.float32(2.0 ** 127)
+    x = dev(rng.uniform(-2, 2, (dim, n)).astype(np.float32))
+    c0, g0 = P.tanh_occupancy_grad(P.TanhNet(dim, H, L, dev(p)), x)
+    c1, g1 = P.tanh_occupancy_grad(P.TanhNet(dim, H, L, dev(big)), x)
+    ref = 2.0 ** 127 * host(g0).astype(np.float64)
+    assert torch.equal(c0, c1) and np.all(ref != 0)
+    assert np.all(np.abs(host(g1) - ref) <= TOL * np.abs(ref))
+    big[-1] = 200.0  # sigma'(s) = 0
+    net = P.TanhNet(dim, H, L, dev(big))
+    assert not bool(P.tanh_occupancy_grad(net, x)[1].any())
+    assert torch.equal(P.tanh_morph_samples(net, x, 5, 0.1), x)
