@@ -689,7 +689,7 @@ __device__ __forceinline__ void arm_wide_body(const pdmp_arm &arm, const uint4 *
             const float gq = zk[0] * v0 + zk[1] * v1 + zk[2] * v2;
             qk = qk - eta * gq;
         } else {
-            float mc = own ? c : -1.0f;
+            float mc = own ? fmaxf(-1.0f, c) : -1.0f;  // a NaN point counts as none
             mc = fmaxf(mc, __shfl_xor(mc, 1, 64));
             mc = fmaxf(mc, __shfl_xor(mc, 2, 64));
             mc = fmaxf(mc, __shfl_xor(mc, 4, 64));
