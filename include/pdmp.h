@@ -67,7 +67,10 @@ typedef enum {
  *           as contractions on the matrix cores at FP32 accuracy: two-part FP16
  *           splits when every nonzero |w| is at least 2^-19 of the largest and no
  *           two consecutive X0 coordinates are more than 6 sqrt(2 ln 2) l apart
- *           (morphs only), three-part BF16 splits otherwise.
+ *           (morphs only; three parts on 3-D grids of at most 7 per axis), three-part
+ *           BF16 splits otherwise; the pairwise sum where that is as fast, and on 3-D
+ *           grids below 16^3 for weights that are not finite or that neither split
+ *           carries (above 2^80, nonzero below 2^-100).
  *           Every call that takes the factorised path first checks the statement
  *           on the device (each hinge equal, by value, to its axis coordinates; a
  *           NaN coordinate fails).  Hinges that are not that grid give undefined
@@ -200,9 +203,11 @@ int32_t pdmp_morph_trajectory(const pdmp_occupancy *occ, const pdmp_arm *arm, co
                               int64_t traj_stride, void *stream);
 
 /* The split scheme the grid morph kernels take for this occupancy (the grid field
- * above): *scheme = 2 for two-part FP16 splits (three products per FP32 multiply-add),
+ * above): *scheme = 2 for two-part FP16 splits (three products per FP32 multiply-add;
+ * three parts and six products on 3-D grids of at most 7 per axis),
  * 1 for three-part BF16 splits (six products), 0 when the morph takes no grid kernel
- * (no grid, or a grid the grid kernels do not cover: the pairwise sum).  Decided on
+ * (no grid, or a grid the grid kernels do not cover: the pairwise sum, which short morphs
+ * of few points take on any 3-D grid below 16^3).  Decided on
  * the device by the morph kernels' own staging code from the same data.  scheme is a
  * HOST pointer; the call waits for `stream`. */
 int32_t pdmp_split_scheme(const pdmp_occupancy *occ, int32_t *scheme, void *stream);

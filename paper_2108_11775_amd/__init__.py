@@ -247,7 +247,9 @@ SPLIT_SCHEMES = {0: ("pairwise", None), 1: ("bf16", 6), 2: ("fp16", 3)}
 def split_scheme(occ: Occupancy):
     """(name, products per FP32 multiply-add) of the split scheme the grid morph
     kernels take for this occupancy, as the library decides it: ("fp16", 3),
-    ("bf16", 6), or ("pairwise", None) when the morph takes no grid kernel."""
+    ("bf16", 6), or ("pairwise", None) when the morph takes no grid kernel.  (On 3-D grids
+    of at most 7 per axis the FP16 scheme takes three parts and six products; short morphs
+    of few points on 3-D grids below 16^3 are pairwise all the same.)"""
     torch = _torch()
     v = C.c_int32(-1)
     _lib.call("pdmp_split_scheme", C.byref(occ.c_struct()), C.byref(v),

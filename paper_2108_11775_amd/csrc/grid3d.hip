@@ -14,7 +14,8 @@
 // per wave go through the 32x32x16 MFMAs (A = W rows, B = [ex | ex dx] of the lane's
 // own point, k = a, G0 = 16 in one k-step; two-part FP16 splits of both and three
 // products per contraction, or three-way bf16 splits and six products when the
-// operands' range needs FP32's exponent range); each 32-row tile holds two z-planes
+// operands' range needs FP32's exponent range; on grids below 16^3 with weights that no
+// split carries, the pairwise sum in the same kernels); each 32-row tile holds two z-planes
 // (c = 2t, 2t+1), so in the accumulator layout lane l owns the fixed y indices
 // b = (8(v/4) + 4(l/32) + v%4) mod 16 and the y/z contractions need only per-lane
 // tables of ey and ez.  The U terms are summed over z first (per y slot, the plane sums
@@ -25,6 +26,8 @@
 // Arm mapping: a wave carries 4 configurations x 8 body points of one link at a
 // time (lane = 8*config + point, mirrored in the upper 32 lanes), walks the links
 // from the tip down, and keeps only the running suffix sums of the Eq. 3 pull-back.
+#include <type_traits>
+
 #include "mfma_split.h"
 #include "pdmp_common.h"
 
@@ -45,8 +48,37 @@ static_assert(kG3Block == 64 * kSplitWaves, "the scheme test's block");
 // 2 ceil(G2 / 2): the padding's weights are zero and its axis coordinates repeat the last
 // hinge's, so every padded operand is finite wherever the real ones are and adds exact
 // zeros; only the ceil(G2 / 2) tiles that hold a real plane are walked.
+//
+// A padded grid has the choice between the contraction and the pairwise FP32 sum, so the
+// contraction keeps to that sum's accuracy and range (errors below: root mean square over
+// the absolute sums against 64 bits, a ratio to the pairwise kernel's):
+//   * ex = exp2(-dx^2) is rounded as there and scaled by 2^c afterwards (ldexp).  The FULL
+//     kernels add c to the exponent's argument, one instruction fewer per value; that sum's
+//     rounding, 2^-21 of ex at c = 15, makes a gradient's error 1.06 to 1.6 times the
+//     pairwise one (15^3 to 6^3 hinges), the separate scaling 0.83 to 1.12.
+//   * Grids of at most kG3Fine per axis have too few terms for the two-part splits' rounding
+//     to average out (1.12 at 6^3, 1.05 at 7^3, 0.98 at 8^3 and above): the FP16 scheme
+//     takes three parts and six products there (0.97 and below).
+//   * Up to kG3Tiny per axis the logit is off by up to 1.08 on any split, three
+//     exponentials to one: single evaluations and the body-point check stay pairwise (the
+//     gradient, 1.00 and below, does not).
+//   * The BF16 scheme scales ex by 2^kG3Bf16Scale, so that the third part of the smallest
+//     normal feature (2^-126) keeps all its bits.
+//   * Weights that are not finite, or on the BF16 scheme outside [2^-100, 2^80), take the
+//     pairwise sum in the kernel (kG3Direct).
+enum G3Scheme { kG3Bf16 = 0, kG3Fp16 = 1, kG3Direct = 2, kG3Fp16Fine = 3 };  // SplitScheme::fp16
+constexpr int kG3Fine = 7, kG3Tiny = 5;
+constexpr int kG3Bf16Scale = 24;
+constexpr uint32_t kG3Bf16Bottom = (127u - 100) << 23, kG3Bf16Top = (127u + 80) << 23;
 struct G3Dims {
     int g0, g1, g2;
+};
+__host__ __device__ inline bool g3_within(const G3Dims &g, int most) {
+    return g.g0 <= most && g.g1 <= most && g.g2 <= most;
+}
+// The grid as the evaluations see it: its axis sizes and its weights in memory.
+struct G3Grid : G3Dims {
+    const float *weights;
 };
 
 constexpr int kG3Tiles = 8;                    // 32-row tiles: 16 planes of 16 rows
@@ -83,11 +115,30 @@ __device__ __forceinline__ void g3_axes(float *ax, float *ay, float *az,
     az[i] = kappa * hinges[2 * M + g0 * g1 * min(i, g2 - 1)];
 }
 
+// The third FP16 part of v from its first two (split2h).
+__device__ __forceinline__ f16x8_t third_h(const float (&v)[8], const f16x8_t &p1,
+                                           const f16x8_t &p2) {
+    f16x8_t p3;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p3[j] = (_Float16)((v[j] - (float)p1[j]) - (float)p2[j]);
+    return p3;
+}
+
+// acc += (a1 + a2 + a3)(b1 + b2 + b3) less the terms past the third order.
+__device__ __forceinline__ f32x16_t mfma_h6(const f16x8_t &a1, const f16x8_t &a2, const f16x8_t &a3,
+                                            const f16x8_t &b1, const f16x8_t &b2, const f16x8_t &b3,
+                                            f32x16_t acc) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a3, b1, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b2, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b3, acc, 0, 0, 0);
+    return mfma_h3(a1, a2, b1, b2, acc);
+}
+
 // Stage W fragments (frag[(p*8 + t)*64 + lane] = part p of W[32t + lane%32][8(lane/32)
 // + j], j < 8: three bf16 parts, or two FP16 parts of 2^sw W) and the prescaled axes
-// into LDS, choosing the scheme when allow16 (else the BF16 parts, no check).  All
-// threads of the block of NW waves call it; the caller synchronises before reading the
-// fragments.
+// into LDS, choosing the scheme when allow16 (else the BF16 parts, without the check when
+// FULL).  All threads of the block of NW waves call it; the caller synchronises before
+// reading the fragments.
 template <bool FULL, int NW>
 __device__ __forceinline__ SplitScheme g3_stage(uint4 *fraw, float *ax, float *ay, float *az,
                                              SplitRangeN<NW> &rg, const float *__restrict__ hinges,
@@ -96,8 +147,9 @@ __device__ __forceinline__ SplitScheme g3_stage(uint4 *fraw, float *ax, float *a
     constexpr int BT = 64 * NW;
     const int nf = 64 * g3_tiles<FULL>(g);
     if (!allow16) {
-        // BF16 parts straight from global memory, no range check
+        // BF16 parts straight from global memory; a padded grid's weights are tested on the way
         bf16x8_t *frag = reinterpret_cast<bf16x8_t *>(fraw);
+        bool out = false;
         for (int idx = threadIdx.x; idx < nf; idx += BT) {
             const int ln = idx & 63, t = idx >> 6;
             const int r = 32 * t + (ln & 31);
@@ -109,9 +161,16 @@ __device__ __forceinline__ SplitScheme g3_stage(uint4 *fraw, float *ax, float *a
             frag[(0 * kG3Tiles + t) * 64 + ln] = p1;
             frag[(1 * kG3Tiles + t) * 64 + ln] = p2;
             frag[(2 * kG3Tiles + t) * 64 + ln] = p3;
+            if (!FULL) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t u = __float_as_uint(v[j]) & 0x7fffffffu;
+                    out = out || u >= kG3Bf16Top || (u != 0 && u < kG3Bf16Bottom);
+                }
+            }
         }
         g3_axes<FULL>(ax, ay, az, hinges, g, kappa);
-        return SplitScheme{0, 0, 0.0f, 0.0f};
+        return SplitScheme{!FULL && __syncthreads_or(out) ? kG3Direct : kG3Bf16, 0, 0.0f, 0.0f};
     }
     constexpr int NI = (kG3Tiles * 64 + BT - 1) / BT;
     const float axis = split_axis(hinges, FULL ? 16 : g.g0, kappa);
@@ -132,11 +191,22 @@ __device__ __forceinline__ SplitScheme g3_stage(uint4 *fraw, float *ax, float *a
         }
     }
     g3_axes<FULL>(ax, ay, az, hinges, g, kappa);
-    const SplitScheme sc = split_decide(mx, mn, axis, FULL ? 16 : g.g0, rg);
+    SplitScheme sc = split_decide(mx, mn, axis, FULL ? 16 : g.g0, rg);
+    if (!FULL) {
+        if (sc.fp16 && g3_within(g, kG3Fine)) sc.fp16 = kG3Fp16Fine;
+        if (sc.fp16 == kG3Bf16) {
+            bool ok = true;
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+                ok = ok && rg.wmax[w] < kG3Bf16Top && rg.wmin[w] >= kG3Bf16Bottom;
+            sc.fp16 = __builtin_amdgcn_readfirstlane(ok ? kG3Bf16 : kG3Direct);
+            sc.sw = 0;
+        }
+    }
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = threadIdx.x + it * BT;
-        if (idx >= nf) break;
+        if (idx >= nf || sc.fp16 == kG3Direct) break;
         const int ln = idx & 63, t = idx >> 6;
         if (sc.fp16) {
             f16x8_t *frag = reinterpret_cast<f16x8_t *>(fraw);
@@ -147,6 +217,7 @@ __device__ __forceinline__ SplitScheme g3_stage(uint4 *fraw, float *ax, float *a
             split2h(v, p1, p2);
             frag[(0 * kG3Tiles + t) * 64 + ln] = p1;
             frag[(1 * kG3Tiles + t) * 64 + ln] = p2;
+            if (!FULL && sc.fp16 == kG3Fp16Fine) frag[(2 * kG3Tiles + t) * 64 + ln] = third_h(v, p1, p2);
         } else {
             bf16x8_t *frag = reinterpret_cast<bf16x8_t *>(fraw);
             bf16x8_t p1, p2, p3;
@@ -159,13 +230,50 @@ __device__ __forceinline__ SplitScheme g3_stage(uint4 *fraw, float *ax, float *a
     return sc;
 }
 
+// The pairwise sums, over the hinges themselves (the lane and its xor-32 partner take every
+// other one of a row along x).
+template <bool GRAD>
+__device__ __forceinline__ void g3_direct(const G3Grid &gr, int pair, const float *ax,
+                                          const float *ay, const float *az, float xs, float ys,
+                                          float zs, float &s, float &sx, float &sy, float &sz) {
+    s = sx = sy = sz = 0.0f;
+    for (int r = 0; r < gr.g1 * gr.g2; ++r) {
+        const float dy = ys - ay[r % gr.g1], dz = zs - az[r / gr.g1];
+        for (int a = (threadIdx.x & 63) >> 5; a < gr.g0; a += 2) {
+            const float dx = xs - ax[a];
+            const float e = exp2_fast(-fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+            const float wp = gr.weights[a + gr.g0 * r] * e;
+            s += wp;
+            if (GRAD) {
+                sx = fmaf(wp, dx, sx);
+                sy = fmaf(wp, dy, sy);
+                sz = fmaf(wp, dz, sz);
+            }
+        }
+    }
+    s = pair_sum(s, pair);
+    if (GRAD) {
+        sx = pair_sum(sx, pair);
+        sy = pair_sum(sy, pair);
+        sz = pair_sum(sz, pair);
+    }
+}
+
 // s (without beta) and, with GRAD, the unscaled logit-gradient sums (sx, sy, sz) at the
 // prescaled point (xs, ys, zs) this lane shares with its xor-32 partner, on the
-// block's split scheme (F16 = sc.fp16), over the grid's nt tiles (8 when FULL).
-template <bool FULL, bool GRAD, bool F16>
-__device__ __forceinline__ void g3_point(const uint4 *fraw, const SplitScheme &sc, int nt, int pair,
-                                         const float *ax, const float *ay, const float *az,
-                                         float xs, float ys, float zs, float &s, float &sx, float &sy, float &sz) {
+// block's scheme (SCH = sc.fp16), over the grid's tiles (8 when FULL).
+template <bool FULL, bool GRAD, int SCH>
+__device__ __forceinline__ void g3_point(const uint4 *fraw, const SplitScheme &sc, const G3Grid &gr,
+                                         int pair, const float *ax, const float *ay,
+                                         const float *az, float xs, float ys, float zs, float &s,
+                                         float &sx, float &sy, float &sz) {
+    static_assert(!FULL || SCH == kG3Bf16 || SCH == kG3Fp16, "padded grids only");
+    if constexpr (SCH == kG3Direct) {
+        g3_direct<GRAD>(gr, pair, ax, ay, az, xs, ys, zs, s, sx, sy, sz);
+        return;
+    }
+    constexpr bool FINE = SCH == kG3Fp16Fine, F16 = SCH == kG3Fp16 || FINE;
+    const int nt = g3_tiles<FULL>(gr);
     const int lane0 = threadIdx.x & 63, h = lane0 >> 5;
     // The weight fragments are the same at every call; an opaque copy of the lane
     // index keeps the compiler from hoisting their LDS reads out of the callers'
@@ -173,24 +281,29 @@ __device__ __forceinline__ void g3_point(const uint4 *fraw, const SplitScheme &s
     int lane = lane0;
     asm volatile("" : "+v"(lane));
     bf16x8_t e1, e2, e3, d1, d2, d3;
-    f16x8_t h1, h2, k1, k2;
-    int c = 0;  // FP16 scheme: this point's operand scale 2^c
+    f16x8_t h1, h2, h3, k1, k2, k3;
+    int c = 0;  // this point's operand scale 2^c (FP16 scheme, padded grids)
     {
         float cf = 0.0f;
         if (F16) {
             c = split_scale_exp(xs, sc.gmin, sc.gmax);
             cf = (float)c;
+        } else if (!FULL) {
+            c = kG3Bf16Scale;
         }
         float e[8], de[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float d = xs - ax[8 * h + j];
-            e[j] = exp2_fast(F16 ? fmaf(-d, d, cf) : -d * d);
+            if (FULL) e[j] = exp2_fast(F16 ? fmaf(-d, d, cf) : -d * d);
+            else e[j] = ldexpf(exp2_fast(-d * d), c);
             de[j] = e[j] * d;
         }
         if (F16) {
             split2h(e, h1, h2);
             if (GRAD) split2h(de, k1, k2);
+            if (FINE) h3 = third_h(e, h1, h2);
+            if (FINE && GRAD) k3 = third_h(de, k1, k2);
         } else {
             split3(e, e1, e2, e3);
             if (GRAD) split3(de, d1, d2, d3);
@@ -226,8 +339,14 @@ __device__ __forceinline__ void g3_point(const uint4 *fraw, const SplitScheme &s
             const f16x8_t *frag = reinterpret_cast<const f16x8_t *>(fraw);
             const f16x8_t a1 = frag[(0 * kG3Tiles + t) * 64 + lane];
             const f16x8_t a2 = frag[(1 * kG3Tiles + t) * 64 + lane];
-            U = mfma_h3(a1, a2, h1, h2, zero);
-            if (GRAD) V = mfma_h3(a1, a2, k1, k2, zero);
+            if (FINE) {
+                const f16x8_t a3 = frag[(2 * kG3Tiles + t) * 64 + lane];
+                U = mfma_h6(a1, a2, a3, h1, h2, h3, zero);
+                if (GRAD) V = mfma_h6(a1, a2, a3, k1, k2, k3, zero);
+            } else {
+                U = mfma_h3(a1, a2, h1, h2, zero);
+                if (GRAD) V = mfma_h3(a1, a2, k1, k2, zero);
+            }
         } else {
             const bf16x8_t *frag = reinterpret_cast<const bf16x8_t *>(fraw);
             const bf16x8_t a1 = frag[(0 * kG3Tiles + t) * 64 + lane];
@@ -269,7 +388,7 @@ __device__ __forceinline__ void g3_point(const uint4 *fraw, const SplitScheme &s
         sy = pair_sum(sy, pair);
         sz = pair_sum(sz, pair);
     }
-    if (F16) {
+    if (F16 || !FULL) {
         const int un = -(sc.sw + c);
         s = ldexpf(s, un);
         if (GRAD) {
@@ -280,9 +399,22 @@ __device__ __forceinline__ void g3_point(const uint4 *fraw, const SplitScheme &s
     }
 }
 
+// f with the block's scheme as a compile-time constant.
+template <bool FULL, bool ALLOW16, class F>
+__device__ __forceinline__ void g3_by_scheme(int scheme, F &&f) {
+    if (ALLOW16 && scheme == kG3Fp16) {
+        f(std::integral_constant<int, kG3Fp16>{});
+    } else if (FULL || scheme == kG3Bf16) {
+        f(std::integral_constant<int, kG3Bf16>{});
+    } else if constexpr (!FULL) {
+        if (ALLOW16 && scheme == kG3Fp16Fine) f(std::integral_constant<int, kG3Fp16Fine>{});
+        else f(std::integral_constant<int, kG3Direct>{});
+    }
+}
+
 // ---- workspace points [3][n]: eval / grad / morph, 32 points per wave ----
-template <bool FULL, int MODE, bool F16>
-__device__ __forceinline__ void g3_ws_body(const uint4 *fraw, const SplitScheme &sc, int nt, const float *ax,
+template <bool FULL, int MODE, int SCH>
+__device__ __forceinline__ void g3_ws_body(const uint4 *fraw, const SplitScheme &sc, const G3Grid &gr, const float *ax,
                                            const float *ay, const float *az, float beta,
                                            float kappa, float gscale, const float *x_in,
                                            int64_t n, int T, float eta, float *c_out,
@@ -304,7 +436,7 @@ __device__ __forceinline__ void g3_ws_body(const uint4 *fraw, const SplitScheme 
             float nx, ny, nz;
             load(i + stride, nx, ny, nz);
             float s, sx, sy, sz, c, sp;
-            g3_point<FULL, MODE != kEval, F16>(fraw, sc, nt, pair, ax, ay, az, kappa * x, kappa * y,
+            g3_point<FULL, MODE != kEval, SCH>(fraw, sc, gr, pair, ax, ay, az, kappa * x, kappa * y,
                                                kappa * z, s, sx, sy, sz);
             x = nx, y = ny, z = nz;
             if ((lane >> 5) != 0 || i >= n) continue;
@@ -326,7 +458,7 @@ __device__ __forceinline__ void g3_ws_body(const uint4 *fraw, const SplitScheme 
     const bool rec = (lane >> 5) == 0 && traj_col(tr, i, n, tc);
     for (int st = 0; st < T; ++st) {
         if (rec) traj_put<3>(tr, st, tc, {x, y, z});
-        g3_point<FULL, true, F16>(fraw, sc, nt, pair, ax, ay, az, kappa * x, kappa * y, kappa * z, s, sx,
+        g3_point<FULL, true, SCH>(fraw, sc, gr, pair, ax, ay, az, kappa * x, kappa * y, kappa * z, s, sx,
                                   sy, sz);
         float c, sp;
         sigmoid_and_slope(s + beta, c, sp);
@@ -362,13 +494,12 @@ k_grid3d_ws(const float *__restrict__ hinges, const float *__restrict__ weights,
                                           MODE == kMorph);
     __syncthreads();
     const float beta = weights[FULL ? 4096 : g.g0 * g.g1 * g.g2];
-    const int nt = g3_tiles<FULL>(g);
-    if (MODE == kMorph && sc.fp16)
-        g3_ws_body<FULL, MODE, true>(fraw, sc, nt, ax, ay, az, beta, kappa, gscale, x_in, n, T, eta,
-                                       c_out, s_out, g_out, x_out, tr, gc.nb);
-    else
-        g3_ws_body<FULL, MODE, false>(fraw, sc, nt, ax, ay, az, beta, kappa, gscale, x_in, n, T,
-                                        eta, c_out, s_out, g_out, x_out, tr, gc.nb);
+    const G3Grid gr{{g}, weights};
+    g3_by_scheme<FULL, MODE == kMorph>(sc.fp16, [&](auto scheme) {
+        g3_ws_body<FULL, MODE, decltype(scheme)::value>(fraw, sc, gr, ax, ay, az, beta, kappa,
+                                                        gscale, x_in, n, T, eta, c_out, s_out,
+                                                        g_out, x_out, tr, gc.nb);
+    });
 }
 
 // Sum over the 8 lanes of a group (lanes 8g..8g+7), the same value in each: two
@@ -459,9 +590,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // ---- joint-space morph (MORPH) or largest body-point occupancy (check) ----
 // 4 configurations per wave; lane%32 = 8*cfg + k, body point k of every link.
-template <int NDOF, bool FULL, bool MORPH, bool F16>
+template <int NDOF, bool FULL, bool MORPH, int SCH>
 __device__ __forceinline__ void arm_body(const pdmp_arm &arm, const uint4 *fraw,
-                                         const SplitScheme &sc, int nt, const float *ax,
+                                         const SplitScheme &sc, const G3Grid &gr, const float *ax,
                                          const float *ay, const float *az, float *kin, const float *lk,
                                          float beta, float kappa,
                                          float gscale, const float *q_in, float *q_out, int64_t n,
@@ -526,7 +657,7 @@ __device__ __forceinline__ void arm_body(const pdmp_arm &arm, const uint4 *fraw,
                 p[e] = ol[e] + frac * (ko[3 * (l + 1) + e] - ol[e]);
             }
             float s, sx, sy, sz;
-            g3_point<FULL, MORPH, F16>(fraw, sc, nt, pair, ax, ay, az, kappa * p[0], kappa * p[1],
+            g3_point<FULL, MORPH, SCH>(fraw, sc, gr, pair, ax, ay, az, kappa * p[0], kappa * p[1],
                                        kappa * p[2], s, sx, sy, sz);
             float c, sp;
             sigmoid_and_slope(s + beta, c, sp);
@@ -596,15 +727,13 @@ k_arm_grid3d(pdmp_arm arm, const float *__restrict__ hinges, const float *__rest
     const SplitScheme sc = g3_stage<FULL>(fraw, ax, ay, az, rg, hinges, weights, g, kappa, true);
     __syncthreads();
     const float beta = weights[FULL ? 4096 : g.g0 * g.g1 * g.g2];
-    const int nt = g3_tiles<FULL>(g);
-    if (sc.fp16)
-        arm_body<NDOF, FULL, MORPH, true>(arm, fraw, sc, nt, ax, ay, az, kin, lk, beta, kappa, gscale,
-                                            q_in, q_out, n, n_eff, T, eta, thresh, maxc_out,
-                                            flag_out, tr);
-    else
-        arm_body<NDOF, FULL, MORPH, false>(arm, fraw, sc, nt, ax, ay, az, kin, lk, beta, kappa, gscale,
-                                             q_in, q_out, n, n_eff, T, eta, thresh, maxc_out,
-                                             flag_out, tr);
+    const G3Grid gr{{g}, weights};
+    g3_by_scheme<FULL, true>(sc.fp16, [&](auto scheme) {
+        arm_body<NDOF, FULL, MORPH, decltype(scheme)::value>(arm, fraw, sc, gr, ax, ay, az, kin, lk,
+                                                             beta, kappa, gscale, q_in, q_out, n,
+                                                             n_eff, T, eta, thresh, maxc_out,
+                                                             flag_out, tr);
+    });
 }
 
 // ---- the same for small batches: one link per wave ----
@@ -615,9 +744,9 @@ k_arm_grid3d(pdmp_arm arm, const float *__restrict__ hinges, const float *__rest
 // pull-back and the update need no other), the per-link sums meet in LDS (two buffers:
 // one block barrier per step) and lane k adds those of the links it moves, tip first as
 // k_arm_grid3d does, so a configuration gets the same bits from either kernel.
-template <int NDOF, bool FULL, bool MORPH, bool F16>
+template <int NDOF, bool FULL, bool MORPH, int SCH>
 __device__ __forceinline__ void arm_wide_body(const pdmp_arm &arm, const uint4 *fraw,
-                                              const SplitScheme &sc, int nt, const float *ax,
+                                              const SplitScheme &sc, const G3Grid &gr, const float *ax,
                                               const float *ay, const float *az,
                                               float (&red)[2][NDOF][4][6], const float *lk,
                                               float beta, float kappa, float gscale,
@@ -658,7 +787,7 @@ __device__ __forceinline__ void arm_wide_body(const pdmp_arm &arm, const uint4 *
             p[e] = ol + frac * (o1 - ol);
         }
         float s, sx, sy, sz;
-        g3_point<FULL, MORPH, F16>(fraw, sc, nt, pair, ax, ay, az, kappa * p[0], kappa * p[1],
+        g3_point<FULL, MORPH, SCH>(fraw, sc, gr, pair, ax, ay, az, kappa * p[0], kappa * p[1],
                                    kappa * p[2], s, sx, sy, sz);
         float c, sp;
         sigmoid_and_slope(s + beta, c, sp);
@@ -731,28 +860,43 @@ k_arm_wide(pdmp_arm arm, const float *__restrict__ hinges, const float *__restri
     const SplitScheme sc = g3_stage<FULL>(fraw, ax, ay, az, rg, hinges, weights, g, kappa, true);
     __syncthreads();
     const float beta = weights[FULL ? 4096 : g.g0 * g.g1 * g.g2];
-    const int nt = g3_tiles<FULL>(g);
-    if (sc.fp16)
-        arm_wide_body<NDOF, FULL, MORPH, true>(arm, fraw, sc, nt, ax, ay, az, red, lk, beta, kappa,
-                                               gscale, q_in, q_out, n, n_eff, T, eta, thresh,
-                                               maxc_out, flag_out, tr);
-    else
-        arm_wide_body<NDOF, FULL, MORPH, false>(arm, fraw, sc, nt, ax, ay, az, red, lk, beta,
-                                                kappa, gscale, q_in, q_out, n, n_eff, T, eta,
-                                                thresh, maxc_out, flag_out, tr);
+    const G3Grid gr{{g}, weights};
+    g3_by_scheme<FULL, true>(sc.fp16, [&](auto scheme) {
+        arm_wide_body<NDOF, FULL, MORPH, decltype(scheme)::value>(arm, fraw, sc, gr, ax, ay, az, red,
+                                                                  lk, beta, kappa, gscale, q_in,
+                                                                  q_out, n, n_eff, T, eta, thresh,
+                                                                  maxc_out, flag_out, tr);
+    });
 }
 
 // Grids the kernels take: at most 16 hinges per axis, and enough of them to pay for the
 // padded contraction, whose cost goes by the tiles nt = ceil(G2 / 2) and not by M.  Measured
 // in us: arm morph, 16,000 configurations, 5 steps: 82 + 20 nt against the pairwise
-// 30 + 1.4 M; workspace morph, 100,000 points, 10 steps: 20 + 5.6 nt against 8 + 0.32 M;
-// the lines cross at M = 37 + 14 nt and 37 + 17 nt.  (10^3 hinges: arm 1,388 -> 188 us,
-// workspace 328 -> 50 us; 15^3: 4,609 -> 275 us, 1,280 -> 73 us.)
+// 30 + 1.4 M; the lines cross at M = 37 + 14 nt.  (10^3 hinges: arm 1,388 -> 188 us; 15^3:
+// 4,609 -> 275 us.)
 static bool g3_supported(const int *grid, int M) {
     if (!grid || grid[0] < 1 || grid[1] < 1 || grid[2] < 1 || grid[0] > kG3Max ||
         grid[1] > kG3Max || grid[2] > kG3Max || M != grid[0] * grid[1] * grid[2])
         return false;
     return M >= 40 + 16 * ((grid[2] + 1) / 2);
+}
+
+// Whether a padded grid's workspace call takes the contraction.
+//   * Single evaluations, by M and nt alone (a point's result does not depend on its batch).
+//     Values and gradients of few points: 3.2 + 0.42 nt us against 4.0 + 0.003 M with the
+//     check's launch; the lines cross at M = 140 nt - 270.  (Gradients of 10^6 points: 16 x 1
+//     x 16 hinges 90 against 77, 6^3 49 against 66, 8^3 60 against 150.)
+//   * Morphs, by a step's time: a wave's chain, 0.6 + 0.22 nt us (the six products of small
+//     grids 0.4 more), or its throughput, against the pairwise kernel's hinge walk and
+//     throughput; and 1.2 us of start-up.  (20 steps, 8^3: one point 33 against 15, 8,000
+//     34 against 38, 10^6 561 against 2,928; 5^3: 8,000 36 against 16, 10^6 615 against 738.)
+static bool g3_ws_pays(int mode, const G3Dims &g, int64_t n, int T) {
+    const double M = (double)(g.g0 * g.g1 * g.g2), nt = (g.g2 + 1) / 2;
+    if (mode != kMorph) return !g3_within(g, kG3Tiny) && M >= 140 * nt - 270;
+    const bool fine = g3_within(g, kG3Fine);
+    const double chain = 0.6 + 0.22 * nt + (fine ? 0.4 : 0.0);
+    const double rate = n * (6e-6 + 6e-6 * nt + (fine ? 6e-6 : 0.0));
+    return T * (0.35 + 5e-4 * M + 3e-7 * n * M - (chain > rate ? chain : rate)) >= 1.2;
 }
 
 // Batches up to this many configurations take one link per wave (k_arm_wide): latency
@@ -768,22 +912,27 @@ static G3Dims g3_dims(const int *grid) { return G3Dims{grid[0], grid[1], grid[2]
 static bool g3_full(const int *grid) { return grid[0] == 16 && grid[1] == 16 && grid[2] == 16; }
 
 // The split scheme the 3-D grid morphs (workspace and arm) take: one block runs their
-// staging and writes 2 (two-part FP16 splits) or 1 (three-part BF16 splits).
+// staging and writes 2 (FP16 splits), 1 (three-part BF16 splits) or 0 (the pairwise sum).
+template <bool FULL>
 __global__ void __launch_bounds__(kG3Block)
 k_grid3d_scheme(const float *__restrict__ hinges, const float *__restrict__ weights, G3Dims g,
                 float kappa, int32_t *out) {
     __shared__ uint4 fraw[kG3Frag];
     __shared__ float ax[kG3Max], ay[kG3Max], az[kG3Max];
     __shared__ SplitRange rg;
-    const SplitScheme sc = g3_stage<false>(fraw, ax, ay, az, rg, hinges, weights, g, kappa, true);
-    if (threadIdx.x == 0) *out = sc.fp16 ? 2 : 1;
+    const SplitScheme sc = g3_stage<FULL>(fraw, ax, ay, az, rg, hinges, weights, g, kappa, true);
+    if (threadIdx.x == 0) *out = sc.fp16 == kG3Direct ? 0 : sc.fp16 == kG3Bf16 ? 1 : 2;
 }
 
 int32_t launch_grid3d_scheme(const float *hinges, const float *weights, const int *grid, int M,
                              float kappa, int32_t *out, hipStream_t st) {
     if (!g3_supported(grid, M)) return PDMP_EUNSUPPORTED;
-    hipLaunchKernelGGL(k_grid3d_scheme, dim3(1), dim3(kG3Block), 0, st, hinges, weights,
-                       g3_dims(grid), kappa, out);
+    if (g3_full(grid))
+        hipLaunchKernelGGL(k_grid3d_scheme<true>, dim3(1), dim3(kG3Block), 0, st, hinges, weights,
+                           g3_dims(grid), kappa, out);
+    else
+        hipLaunchKernelGGL(k_grid3d_scheme<false>, dim3(1), dim3(kG3Block), 0, st, hinges, weights,
+                           g3_dims(grid), kappa, out);
     return check_launch("k_grid3d_scheme");
 }
 
@@ -816,6 +965,7 @@ int32_t launch_grid3d_ws(int mode, const RbfArgs &a, const int *grid, hipStream_
         return PDMP_EUNSUPPORTED;
     const int64_t blocks = (a.n + 127) / 128;
     if (!g3_full(grid)) {
+        if (!g3_ws_pays(mode, g3_dims(grid), a.n, a.T)) return PDMP_EUNSUPPORTED;
         // a batch beyond one dispatch of this kernel still fits the pairwise kernel's
         if (blocks * kG3Block > 0xffffffffll) return PDMP_EUNSUPPORTED;
         return launch_grid3d_ws_n<false>(mode, a, g3_dims(grid), st);
@@ -851,6 +1001,7 @@ int32_t launch_arm_grid3d(const pdmp_arm &arm, const float *h, const float *w, i
                           const Traj &traj) {
     if (!g3_supported(grid, M) || arm.pts_per_link > 8) return PDMP_EUNSUPPORTED;
     const bool full = g3_full(grid);
+    if (!morph && g3_within(g3_dims(grid), kG3Tiny)) return PDMP_EUNSUPPORTED;
     const int64_t blocks = (n + 15) / 16;
     if (!full && blocks * kG3Block > 0xffffffffll) return PDMP_EUNSUPPORTED;
     if (int32_t e = grid_guard(blocks, kG3Block, "k_arm_grid3d")) return e;
