@@ -838,7 +838,7 @@ __device__ __forceinline__ void arm_wide_body(const pdmp_arm &arm, const uint4 *
 
 template <int NDOF, bool FULL, bool MORPH>
 __global__ void __launch_bounds__(64 * NDOF)
-__attribute__((amdgpu_waves_per_eu(NDOF > 1 ? 3 : 1)))
+__attribute__((amdgpu_waves_per_eu(3)))
 k_arm_wide(pdmp_arm arm, const float *__restrict__ hinges, const float *__restrict__ weights,
            G3Dims g, float kappa, float gscale, const float *q_in, float *q_out, int64_t n, int T,
            float eta, const uint32_t *__restrict__ n_active, float thresh, float *maxc_out,
@@ -899,14 +899,22 @@ static bool g3_ws_pays(int mode, const G3Dims &g, int64_t n, int T) {
     return T * (0.35 + 5e-4 * M + 3e-7 * n * M - (chain > rate ? chain : rate)) >= 1.2;
 }
 
-// Batches up to this many configurations take one link per wave (k_arm_wide): latency
-// binds them, and a 7-link block of the wide kernel holds a CU (3 waves per SIMD), so its
-// time goes by rounds of 256 blocks = 1,024 configurations, where k_arm_grid3d's is flat
-// up to one wave per SIMD (4,096).  Morph of 10 steps, 7 links, 16^3 hinges, us, wide
-// against one wave per 4 configurations: 500: 48.6 / 148; 1,000: 51 / 149; 2,000: 98 / 149;
-// 3,000: 144 / 149; 4,000: 190 / 154.  The check is equal up to 3,000 (18 us with its
-// launches) and slower above.
-constexpr int64_t kArmWideMax = 3072;
+// Whether a batch takes one link per wave (k_arm_wide): a step's latency is then that of one
+// link instead of n_dof, but blocks of 5 links and more hold a CU (3 waves per SIMD; two of
+// fewer links share it), so its time goes by rounds of 256 blocks = 1,024 configurations,
+// where k_arm_grid3d's is flat up to one wave per SIMD (4,096).  From sweeps of 1 to 8 links,
+// 16^3 hinges, 1 to 16,000 configurations (us): k_arm_grid3d 8 + T (0.6 + 1.9 n_dof); wide 8 +
+// 4 (r - 1) + T (0.2 + 4 r) in r rounds, of up to 4 links 8 + 2 (r - 1) + T (1.3 + 1.4 r).
+// (10 steps, 7 links: 1,000 configurations 53 against 146, 2,000 95 / 146, 3,000 138 / 147,
+// 4,000 181 / 152; one step of 3,000: 28 / 23.  One link: 37 / 32 at any size.)  The check: 10,
+// 13, 17 us in 1, 2, 3 rounds against 7.9 + 1.3 n_dof (padded grids, two links: 10.4 / 9.4).
+static bool arm_wide_pays(int n_dof, bool full, bool morph, int64_t n, int T) {
+    if (n_dof < 2 || n > 3072) return false;
+    const int r = (int)((n + 1023) / 1024);
+    if (!morph) return 5 * r <= 2 * n_dof + (full ? 2 : 0);
+    return n_dof > 4 ? T * (0.4 + 1.9 * n_dof - 4 * r) >= 4 * (r - 1)
+                     : T * (1.9 * n_dof - 0.7 - 1.4 * r) >= 2 * (r - 1);
+}
 
 static G3Dims g3_dims(const int *grid) { return G3Dims{grid[0], grid[1], grid[2]}; }
 static bool g3_full(const int *grid) { return grid[0] == 16 && grid[1] == 16 && grid[2] == 16; }
@@ -983,10 +991,12 @@ static int32_t launch_arm_grid3d_n(const pdmp_arm &arm, const float *h, const fl
 #define PDMP_ARM(K, G, B)                                                                        \
     hipLaunchKernelGGL(K, dim3((unsigned)(G)), dim3(B), 0, st, arm, h, w, d, kappa, gscale, qi, qo, \
                        n, T, eta, n_active, thresh, maxc, flag, traj)
-    if (n <= kArmWideMax) {
-        if (morph) PDMP_ARM((k_arm_wide<NDOF, FULL, true>), (n + 3) / 4, 64 * NDOF);
-        else PDMP_ARM((k_arm_wide<NDOF, FULL, false>), (n + 3) / 4, 64 * NDOF);
-        return check_launch("k_arm_wide");
+    if constexpr (NDOF > 1) {
+        if (arm_wide_pays(NDOF, FULL, morph, n, T)) {
+            if (morph) PDMP_ARM((k_arm_wide<NDOF, FULL, true>), (n + 3) / 4, 64 * NDOF);
+            else PDMP_ARM((k_arm_wide<NDOF, FULL, false>), (n + 3) / 4, 64 * NDOF);
+            return check_launch("k_arm_wide");
+        }
     }
     if (morph) PDMP_ARM((k_arm_grid3d<NDOF, FULL, true>), (n + 15) / 16, kG3Block);
     else PDMP_ARM((k_arm_grid3d<NDOF, FULL, false>), (n + 15) / 16, kG3Block);
@@ -1002,6 +1012,10 @@ int32_t launch_arm_grid3d(const pdmp_arm &arm, const float *h, const float *w, i
     if (!g3_supported(grid, M) || arm.pts_per_link > 8) return PDMP_EUNSUPPORTED;
     const bool full = g3_full(grid);
     if (!morph && g3_within(g3_dims(grid), kG3Tiny)) return PDMP_EUNSUPPORTED;
+    // one link, many configurations: a pairwise step of 16,000 is 0.04 M us (M = 125: 5.4, 216:
+    // 8.7), of the contraction 5.4 to 7, with 6 us more to start (T = 1: 10.5 against 16.2)
+    if (!full && morph && arm.n_dof == 1 && n > 8192 && M <= (T > 2 ? 128 : 256))
+        return PDMP_EUNSUPPORTED;
     const int64_t blocks = (n + 15) / 16;
     if (!full && blocks * kG3Block > 0xffffffffll) return PDMP_EUNSUPPORTED;
     if (int32_t e = grid_guard(blocks, kG3Block, "k_arm_grid3d")) return e;
