@@ -31,12 +31,20 @@ int32_t launch_grid_check(int dim, const float *hinges, int M, const int *grid, 
     return check_launch("k_grid_check");
 }
 
-// The mismatch word's address on each device: a kernel of another file cannot name it.
+// The mismatch word's address on each device: a kernel of another file cannot name it.  (A
+// launch of the check's own takes the word of the device that it runs on.)
 static std::atomic<uint32_t *> g_word[64];
 
 static uint32_t *mismatch_word(hipStream_t st) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    // a stream of another device: its kernels must not write to this one's word
+    hipDevice_t on = dev;
+    if (st && hipStreamGetDevice(st, &on) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (on != dev) return nullptr;
     uint32_t *p = g_word[dev].load(std::memory_order_acquire);
     if (p) return p;
     // first call on the device; left for a later one while the stream is captured

@@ -1,0 +1,72 @@
+"""Host checks of what the library launches, on the CPU: the library runs in a child process
+against tests/fake_hip.cpp, which records the launches and has no device."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes as C, json, sys
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.fake_launches.restype = C.c_char_p
+from paper_2108_11775_amd import _lib
+lib = _lib.load()
+ptr = C.c_void_p(1 << 20)  # device addresses: no kernel runs, nothing reads them
+def occ(dim, M, grid=(0, 0, 0)):
+    return C.byref(_lib.pdmp_occupancy(dim, M, ptr, ptr, 0.5, tuple(grid) + (0,) * (3 - len(grid))))
+def stream(dev):
+    return C.c_void_p(0x1000 * (dev + 1))
+def launches(name, *args):
+    fake.fake_launches()
+    st = getattr(lib, name)(*args)
+    out = []
+    for line in fake.fake_launches().decode().splitlines():
+        kernel, grid, block, lds = line.rsplit(" ", 3)
+        out.append(dict(kernel=kernel, grid=[int(v) for v in grid[5:].split(",")],
+                        block=int(block[6:]), lds=int(lds[4:])))
+    assert st == 0, (st, lib.pdmp_last_error())
+    return out
+"""
+
+
+@pytest.fixture(scope="session")
+def fake_hip(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"),
+                    "-o", lib], check=True)
+    return lib
+
+
+def run(fake_hip, body):
+    """The JSON that `body` prints (after PRELUDE)."""
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, fake_hip], capture_output=True, text=True,
+                       cwd=os.path.dirname(HERE), timeout=120)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+def names(ls):
+    return [l["kernel"].split("(")[0].split("<")[0].split("::")[-1] for l in ls]
+
+
+def test_grid_check_stays_on_the_stream_s_device(fake_hip):
+    """The check's blocks go with the call's launch only where the word they report to is the
+    current device's; on a stream of another device the check is a launch of its own, whose
+    kernel names its own device's word."""
+    out = run(fake_hip, """
+o = occ(2, 900, (30, 30))
+calls = [("pdmp_occupancy_grad", o, ptr, 48, ptr, ptr), ("pdmp_occupancy_eval", o, ptr, 48, ptr, ptr),
+         ("pdmp_morph_samples", o, None, ptr, ptr, 48, 5, 0.1),
+         ("pdmp_occupancy_grad", occ(3, 4096, (16, 16, 16)), ptr, 48, ptr, ptr)]
+print(json.dumps([[launches(*c, s) for s in (None, stream(0), stream(1))] for c in calls]))
+""")
+    for null, own, other in out:
+        assert len(names(null)) == len(names(own)) == 1
+        assert names(other) == ["k_grid_check"] + names(own)
+        assert other[1]["grid"][0] < own[0]["grid"][0]
+
+
