@@ -8,7 +8,7 @@
 // Mapping.  The work is FP32 VALU + v_exp_f32 bound (one exp and 3*DIM+2 VALU per
 // sample-hinge pair), not HBM bound: samples stream in once and out once.
 //   * Hinges live in LDS for the whole launch when they fit (64 KiB: 4096 3-D or
-//     5460 2-D hinges), staged as chunks of four: DIM float4 rows of prescaled
+//     5504 2-D hinges), staged as chunks of four: DIM float4 rows of prescaled
 //     coordinates kappa*h and one float4 row of weights, so one ds_read_b128 per row
 //     feeds four hinges.  Larger hinge sets are streamed
 //     through LDS tile by tile inside each step.
@@ -122,7 +122,7 @@ k_rbf(const float *__restrict__ hinges, const float *__restrict__ weights, int M
       int T, float eta, float *c_out, float *s_out, float *g_out, float *x_out,
       const float *__restrict__ g_in, int chain, int cps, Traj tr) {
     constexpr int IW = chunk_iw<G>();
-    constexpr int TILE = tile_chunks<DIM>() / 16 * 16;
+    constexpr int TILE = rbf_tile_chunks<DIM>();
     extern __shared__ float4 lds[];
 
     const int nchunks_all = chunks_for(M);
@@ -239,7 +239,7 @@ k_rbf(const float *__restrict__ hinges, const float *__restrict__ weights, int M
 
 template <int DIM, int SPL, int G, int BLOCK, int MODE>
 static int32_t launch_rbf_v(const RbfArgs &a, hipStream_t st) {
-    constexpr int TILE = tile_chunks<DIM>() / 16 * 16, IW = chunk_iw<G>();
+    constexpr int TILE = rbf_tile_chunks<DIM>(), IW = chunk_iw<G>();
     const int nchunks = chunks_for(a.M);
     const int splits = a.splits > 1 ? a.splits : 1;
     const int cps = (nchunks + splits - 1) / splits;

@@ -70,3 +70,23 @@ print(json.dumps([[launches(*c, s) for s in (None, stream(0), stream(1))] for c 
         assert other[1]["grid"][0] < own[0]["grid"][0]
 
 
+
+def test_hinges_that_fit_the_lds_are_not_split(fake_hip):
+    """2-D sets of up to 5,460 hinges (64 KiB as float4 rows of three) stay in LDS over a
+    morph's steps, and so do the ranges of points of a weight gradient."""
+    out = run(fake_hip, """
+print(json.dumps([[launches("pdmp_morph_samples", occ(2, M), None, ptr, ptr, n, 5, 0.1, None)
+                   for n in (300, 8000, 40000, 1 << 21)] for M in (5441, 5460)]))
+""")
+    for M, calls in zip((5441, 5460), out):
+        for ls in calls:
+            assert names(ls) == ["k_rbf"] and ls[0]["lds"] >= (M + 3) // 4 * 48, (M, ls)
+    # 1,365 chunks of points per range: 21,840 points and one hinge give ranges of a tile at most
+    (ls,) = run(fake_hip, """
+ws = lib.pdmp_bwd_workspace_size(2, 20000, 1365 * 4 * 60)
+print(json.dumps([launches("pdmp_occupancy_bwd", occ(2, 20000), ptr, 1365 * 4 * 60, ptr, None, ptr, None,
+                           ptr, ws, None)]))
+""")
+    rbf = [l for l in ls if names([l]) == ["k_rbf"]]
+    chunks = -(-1365 * 60 // rbf[0]["grid"][1])
+    assert rbf[0]["lds"] >= chunks * 48, rbf
