@@ -13,6 +13,8 @@
 // point set is split into ranges of at most one LDS tile; each range writes a
 // partial row and the rows are summed in a fixed order.  Every reduction here is
 // fixed-order (block-range sums, then one block), so results are deterministic.
+#include <algorithm>
+
 #include "pdmp_common.h"
 #include "rbf_split.h"
 
@@ -270,9 +272,10 @@ static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Splits of the point set for Phi^T g: each range within one LDS tile, and enough block
 // rows (256 or 512 hinges each) to fill the chip, as far as the workspace's rows go.
+static int64_t range_tile(int dim) { return dim == 2 ? tile_chunks<2>() : tile_chunks<3>(); }
 static int bwd_splits(int dim, int M, int64_t n, int64_t hinges_per_block) {
     const int64_t nch = (n + 3) / 4;
-    const int tile = dim == 2 ? tile_chunks<2>() : tile_chunks<3>();
+    const int64_t tile = range_tile(dim);
     int64_t s = (nch + tile - 1) / tile;
     const int64_t hb = (M + hinges_per_block - 1) / hinges_per_block;
     const int64_t want = (1024 + hb - 1) / hb;
@@ -280,6 +283,24 @@ static int bwd_splits(int dim, int M, int64_t n, int64_t hinges_per_block) {
     if (s > nch) s = nch;
     if (s < 1) s = 1;
     return (int)s;
+}
+
+// Hinges per block of the pairwise weight gradient, lanes being hinges.  Two per lane halve the
+// LDS reads that bind it (3-D, 600,000 points, 1,500 hinges: 0.78 of the time with one), but
+// pay from 1,500 hinges and 65,536 points on (1,000 hinges, 200,000 points: 1.23), where the
+// last block of 512 idles for at most an eighth of the work, and where the launch fills its
+// rounds of as many blocks as the LDS holds no worse (3-D, 6,000 hinges, 300,000 points: 1,032
+// blocks on 512 slots against 1,776: 1.13).
+static int wgrad_hinges_per_block(int dim, int64_t M, int64_t n) {
+    const int64_t two = (M + 511) / 512 * 512, one = (M + 255) / 256 * 256;
+    if (M < 1500 || n < 65536 || 8 * two > 9 * one) return 256;
+    auto fill = [&](int64_t per) {
+        const int64_t s = bwd_splits(dim, (int)M, n, per), blocks = (M + per - 1) / per * s;
+        const int64_t lds = ((n + 3) / 4 + s - 1) / s * 16 * (dim + 1);
+        const int64_t slots = 256 * std::min<int64_t>(8, (int64_t)160 * 1024 / lds);
+        return (double)blocks / (double)((blocks + slots - 1) / slots * slots);
+    };
+    return fill(512) >= fill(256) ? 512 : 256;
 }
 
 // Partial rows of a workspace: for the pairwise splits and for the grid kernels.
@@ -297,7 +318,7 @@ size_t bwd_ws_bytes(int dim, int M, int64_t n) {
 // weighted set and the hinges the lanes; S ranges of points give S partial rows.
 static int32_t launch_pairwise_wgrad(int dim, const float *hinges, int M, float kappa,
                                      float gscale, const float *x, int64_t n, const float *gw,
-                                     float *part, int S, hipStream_t st) {
+                                     float *part, int S, int per, hipStream_t st) {
     RbfArgs a;
     a.hinges = x;
     a.weights = gw;
@@ -309,7 +330,7 @@ static int32_t launch_pairwise_wgrad(int dim, const float *hinges, int M, float 
     a.n = M;
     a.s_out = part;
     a.splits = S;
-    return launch_rbf(dim, kEval, a, st);
+    return S > 1 ? launch_rbf_wgrad(dim, a, per, st) : launch_rbf(dim, kEval, a, st);
 }
 
 size_t bce_ws_bytes(int64_t) { return align256(kRedMaxBlocks * sizeof(double)); }
@@ -327,9 +348,10 @@ static int32_t launch_wgrad_rows(int dim, const float *hinges, int M, const int 
     const int32_t e = launch_grid_wgrad(dim, hinges, M, grid, kappa, x, n, gw, part, &S, st);
     if (e != PDMP_EUNSUPPORTED) return e;
     const int64_t most = (int64_t)bwd_rows(dim, M, n);
-    S = bwd_splits(dim, M, n, wgrad_hinges_per_block(M));
+    const int per = wgrad_hinges_per_block(dim, M, n);
+    S = bwd_splits(dim, M, n, per);
     if (S > most) S = (int)most;
-    return launch_pairwise_wgrad(dim, hinges, M, kappa, gscale, x, n, gw, part, S, st);
+    return launch_pairwise_wgrad(dim, hinges, M, kappa, gscale, x, n, gw, part, S, per, st);
 }
 
 // Up to this many points one block sums g beside the blocks that sum the rows (10^5: 7.1 us,

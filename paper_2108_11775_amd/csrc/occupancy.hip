@@ -123,6 +123,10 @@ k_rbf(const float *__restrict__ hinges, const float *__restrict__ weights, int M
       const float *__restrict__ g_in, int chain, int cps, Traj tr) {
     constexpr int IW = chunk_iw<G>();
     constexpr int TILE = rbf_tile_chunks<DIM>();
+    // values of one sample are few instructions per LDS read: two chunks at a time hide its latency
+    // (26,000 samples, 2,600 hinges: 19.3 -> 18.4 us; weight gradient, 2^20 points, 700
+    // hinges: 244 -> 212)
+    constexpr int UN = MODE == kEval && SPL == 1 ? 2 : 1;
     extern __shared__ float4 lds[];
 
     const int nchunks_all = chunks_for(M);
@@ -178,6 +182,7 @@ k_rbf(const float *__restrict__ hinges, const float *__restrict__ weights, int M
                 __syncthreads();
             }
             const float4 *ch = lds + chunk_at<DIM, IW>(lg, 0);
+#pragma unroll UN
             for (int c = lg; c < nc; c += G, ch += G * (DIM + 1))
                 chunk_accumulate<DIM, SPL, IW, MODE != kEval>(ch, xs, as, ag);
         }
@@ -255,54 +260,68 @@ static int32_t launch_rbf_v(const RbfArgs &a, hipStream_t st) {
     return check_launch("k_rbf");
 }
 
-// Lanes per sample (G), samples per lane (SPL) and block size, by what binds the launch.
-//   * Few samples: the length of a lane's hinge walk.  G = 64 up to 5,000 samples (morph
-//     step in us, 1,000 samples and 4,000 hinges: 2.4 against 7.8 with G = 16; 4,096: 5.1
-//     against 7.8; the lines cross between 5,000 and 8,000).
+// Lanes per sample (G), samples per lane (SPL) and block size, by what binds the launch; us.
+//   * Few samples: the length of a lane's hinge walk.  G = 64 up to 1,000 + 8 M samples, at
+//     most 5,000 (morph step, 1,000 samples and 4,000 hinges: 2.4 against 7.8 with G = 16;
+//     4,096: 5.1 against 7.8; the lines cross between 5,000 and 8,000 there, with 200 hinges
+//     between 3,000 and 5,000, with 100 between 1,500 and 3,000; up to 64 hinges the lanes
+//     past the last chunk idle and the exchanges remain: 8 steps, 30 hinges, 5,000 samples: 8.8
+//     against 4.8).  512 threads for single evaluations, which stage the hinges for as little
+//     work as one step, and for 53 KiB and more of hinges (below; 6,000 hinges, 5,000 samples,
+//     4 steps: 119 -> 62).
 //   * More: the LDS reads of hinges and the waves in flight.  16 lanes that read 16
-//     consecutive chunks leave both clear at every size measured (us per 10 steps, 40,001
-//     samples, 2-D: 4,000 hinges 368, four lanes per sample 512; 1,000 hinges 99 against
-//     131; 600,000 samples, 4,000 hinges: 5,125, one lane per sample and two samples per
-//     lane 9,060).  512 threads keep 40 KiB and more of hinges from holding the CU to few waves
-//     (40,001 samples, 3-D, 4,000 hinges: 471 against 534), unless 256 CUs of such blocks
-//     then end on a round that 256 threads would not need (8,523 samples: 238 against 195).
-//     From 65,536 samples on the rounds are many and 512 threads win alike (evaluations of
-//     100,003 samples, 4,096 hinges: 80 against 108; 3-D 103 against 150).
-//   * Few hinges and many samples: the exchanges of a step's end.  Eight lanes below 600
-//     hinges from 30,000 samples on (us per 8 steps, 40,001 samples, 200 hinges: 25
-//     against 29 with 16 lanes; 100,003 samples, 400 hinges: 85 against 94 and, with four
-//     lanes, 97; below 30,000 samples 16 lanes fill the chip better) and below 1,200 from
-//     60,000 on (65,536 samples, 1,044 hinges: 130 against 138; 300,000, 850: 458 against
-//     480); four lanes below 600 hinges from 200,000 on (300,000 samples, 200 hinges: 119
-//     against 128 with eight).
+//     consecutive chunks leave both clear (10 steps, 40,001 samples, 2-D: 4,000 hinges 368, four
+//     lanes per sample 512; 1,000 hinges 99 against 131; 600,000 samples, 4,000 hinges:
+//     5,125, one lane per sample and two samples per lane 9,060).  512 threads stage the
+//     hinges half as often and keep many of them from holding the CU to few waves, but 256 CUs
+//     of such blocks may end on a round of 32 samples per CU that 256 threads would not need.
+//     512 where they do not (14,000 samples, 2,000 hinges, one evaluation: 0.92 of the time;
+//     10,000: 1.01 to 1.05, over 8 steps 1.16); always where two blocks' hinges at most fit a
+//     CU (53 KiB; 10,000 samples, 5,000 hinges: 0.72), which includes hinges past one tile
+//     (26,000 samples, 6,000 hinges, 4 steps: 281 -> 200), from 65,536 samples on above 40 KiB
+//     (evaluations of 100,003 samples, 4,096 hinges: 80 against 108), and for single
+//     evaluations of 20,000 and more above 32 KiB (26,000, 3,000 hinges: 0.93).  64 lanes again
+//     between 8,192 and 11,000 samples, where a second round of 16 lanes would be half
+//     empty (10,000 samples, 4,000 hinges, 8 steps: 0.77 of the time; 1,400: 0.91; 600: 1.11).
+//   * Few hinges: the exchanges of a step's end, so as few lanes as fill the chip (two waves
+//     per SIMD).  Below 600 hinges 8 from 12,000 samples (16,000, 200 hinges, 8 steps: 14.5
+//     against 18.3 with 16), below 64 always (16 lanes walk half a chunk); from 30,000 four
+//     below 300 hinges and 8 above (30,000, 100 hinges, 8 steps: 14.7 against 18.2 with 8); one
+//     where the blocks of 256 samples fill nine tenths of their rounds (131,072, 30 hinges, 8
+//     steps: 13.5 against 19.1 with 8; 200,000, 200 hinges, three blocks and a bit per CU: 100
+//     against four lanes' 94); one always for 8 hinges and fewer, and from 120,000 below 64.  8 below 1,200 hinges from
+//     60,000 on (65,536 samples, 1,044 hinges: 130 against 138; 300,000, 850: 458 against 480).
 //   * Batches that fill whole rounds of 512 blocks of 2,048 samples: one lane per sample, two
-//     samples per lane, no exchanges (2^20 samples, 5 steps, us: 900 hinges 1,024 against
+//     samples per lane, no exchanges (2^20 samples, 5 steps: 900 hinges 1,024 against
 //     1,127, 3-D 4,096 hinges 5,884 against 6,143); a poorly filled last round costs more than
-//     that (600,000 samples above).  Also from 2^27 samples, where 16 threads per sample
+//     that (600,000 samples above; single evaluations lose less, 1,500,000 samples on 2,000 3-D
+//     hinges, seven tenths filled: 600 against 687).  Also from 2^27 samples, where 16 threads per sample
 //     would pass one dispatch.
-//   * A single evaluation stages the hinges for as little work as one step: 512 threads, so
-//     half the blocks do (8,000 to 16,384 samples, 2-D, 850 to 1,044 hinges: 7.1 to 8.1 us
-//     against 7.7 to 8.6 with 256).
-//   * A weight gradient (splits): lanes are hinges and every lane reads the same points
-//     (rbf_split.h).
 template <int DIM, int MODE>
 static int32_t launch_rbf_dim(const RbfArgs &a, hipStream_t st) {
-    if (MODE == kEval && a.splits > 1)
-        return wgrad_hinges_per_block(a.n) == 512 ? launch_rbf_v<DIM, 2, 1, 256, MODE>(a, st)
-                                                  : launch_rbf_v<DIM, 1, 1, 256, MODE>(a, st);
     const bool single = MODE != kMorph || a.T <= 1;
-    const int64_t b = (a.n + 2047) / 2048, slots = (b + 511) / 512 * 512;
-    if ((a.n >= (1 << 19) && 10 * b >= 9 * slots) || a.n >= (1 << 27))
-        return launch_rbf_v<DIM, 2, 1, 1024, MODE>(a, st);
-    if (a.n <= 5000)
-        return single ? launch_rbf_v<DIM, 1, 64, 512, MODE>(a, st)
-                      : launch_rbf_v<DIM, 1, 64, 256, MODE>(a, st);
-    if (a.M < 600 && a.n >= 200000) return launch_rbf_v<DIM, 1, 4, 256, MODE>(a, st);
-    if ((a.M < 600 && a.n >= 30000) || (a.M < 1200 && a.n >= 60000))
+    const int lds = chunks_for(a.M) * ChunkLayout<DIM>::kBytes;
+    const bool two = lds > 53 * 1024;  // two blocks at most share a CU
+    // samples in blocks of `per` fill at least tenths/10 of their rounds of `slots` blocks
+    auto fills = [&](int64_t per, int64_t slots, int tenths) {
+        const int64_t b = (a.n + per - 1) / per;
+        return 10 * b >= tenths * ((b + slots - 1) / slots * slots);
+    };
+    const bool wide = a.n >= (1 << 19) && (a.M <= 8 || fills(2048, 512, MODE != kMorph ? 7 : 9));
+    if (!(wide && (a.M <= 8 || a.M >= 600)) && a.n < (1 << 27) &&
+        (a.M <= 8 || (a.n >= 120000 && (a.M < 64 || (a.M < 600 && fills(256, 256, 9))))))
+        return launch_rbf_v<DIM, 1, 1, 256, MODE>(a, st);
+    if (wide || a.n >= (1 << 27)) return launch_rbf_v<DIM, 2, 1, 1024, MODE>(a, st);
+    if (a.M >= 64 && a.n <= 5000 && a.n <= 1000 + 8 * (int64_t)a.M)
+        return single || two ? launch_rbf_v<DIM, 1, 64, 512, MODE>(a, st)
+                             : launch_rbf_v<DIM, 1, 64, 256, MODE>(a, st);
+    if (a.M < 300 && a.n >= 30000) return launch_rbf_v<DIM, 1, 4, 256, MODE>(a, st);
+    if (a.M < 64 || (a.M < 600 && a.n >= 12000) || (a.M < 1200 && a.n >= 60000))
         return launch_rbf_v<DIM, 1, 8, 256, MODE>(a, st);
+    if (a.M >= 1400 && a.n > 8192 && a.n <= 11000) return launch_rbf_v<DIM, 1, 64, 512, MODE>(a, st);
     auto round_up = [&](int64_t per) { return (a.n + 256 * per - 1) / (256 * per) * per; };
-    if (single || (chunks_for(a.M) * ChunkLayout<DIM>::kBytes > 40 * 1024 &&
-                   (a.n >= 65536 || round_up(32) <= round_up(16))))
+    if (two || round_up(32) <= round_up(16) ||
+        (lds > 40 * 1024 && a.n >= 65536) || (lds > 32 * 1024 && single && a.n >= 20000))
         return launch_rbf_v<DIM, 1, 16, 512, MODE>(a, st);
     return launch_rbf_v<DIM, 1, 16, 256, MODE>(a, st);
 }
@@ -319,6 +338,15 @@ static int32_t launch_rbf_mode(int mode, const RbfArgs &a, hipStream_t st) {
 
 int32_t launch_rbf(int dim, int mode, const RbfArgs &a, hipStream_t st) {
     return dim == 2 ? launch_rbf_mode<2>(mode, a, st) : launch_rbf_mode<3>(mode, a, st);
+}
+
+// A weight gradient: lanes are hinges (rbf_split.h) and every lane reads the same points.
+int32_t launch_rbf_wgrad(int dim, const RbfArgs &a, int hinges_per_block, hipStream_t st) {
+    if (hinges_per_block == 512)
+        return dim == 2 ? launch_rbf_v<2, 2, 1, 256, kEval>(a, st)
+                        : launch_rbf_v<3, 2, 1, 256, kEval>(a, st);
+    return dim == 2 ? launch_rbf_v<2, 1, 1, 256, kEval>(a, st)
+                    : launch_rbf_v<3, 1, 1, 256, kEval>(a, st);
 }
 
 int32_t launch_occ_any(int dim, int mode, const RbfArgs &a, const int *grid, hipStream_t st) {

@@ -15,12 +15,8 @@ namespace pdmp {
 template <int DIM>
 constexpr int rbf_tile_chunks() { return (tile_chunks<DIM>() + 15) / 16 * 16; }
 
-// Lanes are hinges there: two per lane halve the LDS reads that bind it, unless the last
-// block of 512 then idles for more than an eighth of the work (40,001 points, 3-D, 1,044
-// hinges: 1,536 lanes' work in three such blocks, 1,280 in five of 256).
-inline int wgrad_hinges_per_block(int64_t M) {
-    const int64_t two = (M + 511) / 512 * 512, one = (M + 255) / 256 * 256;
-    return 8 * two <= 9 * one ? 512 : 256;
-}
+// The pairwise weight gradient: a.M points as weighted hinges in a.splits ranges, a.n hinges
+// as the lanes' samples, 256 or 512 of them per block.
+int32_t launch_rbf_wgrad(int dim, const RbfArgs &a, int hinges_per_block, hipStream_t st);
 
 }  // namespace pdmp

@@ -208,3 +208,43 @@ def test_pairwise_lane_splits(dim, n, M):
                                  (65537, 3999)])
 def test_pairwise_eight_and_four_lanes(dim, n, M):
     test_pairwise_lane_splits(dim, n, M)
+
+
+# either side of every other line of the rule: 64 lanes, one lane, 512 threads, one LDS tile, and
+# the weight gradient's two hinges per lane
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n,M", [(11999, 299), (12001, 299), (30001, 300), (131071, 320), (9001, 1400),
+                                 (9001, 1399), (11001, 3000), (20001, 2300), (700, 5505), (66001, 1530)])
+def test_pairwise_launch_lines(dim, n, M):
+    test_pairwise_lane_splits(dim, n, M)
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n,M", [(7, 8), (8191, 9), (1512, 64), (1513, 64), (11999, 63), (30001, 63),
+                                 (120001, 40), (600001, 3), (1048576, 63)])
+def test_pairwise_few_hinges(dim, n, M):
+    """Fewer hinges than the lanes of larger sets: the same as with hinges of weight 0 added, which
+    takes other lanes per sample; a sum of M terms in another order is off by M 2^-24 of its
+    absolute sum on either side."""
+    require_gpu()
+    import torch
+    rng = np.random.default_rng(M + n)
+    b, ell = (10.0, 2.5) if dim == 2 else (1.0, 0.4)
+    h = rng.uniform(-b, b, (dim, 700)).astype(np.float32)
+    wb = np.zeros(701, np.float32)
+    wb[:M], wb[-1] = rng.normal(0, 1, M), 0.1
+    x = dev(rng.uniform(-b, b, (dim, n)).astype(np.float32))
+    up = dev(rng.normal(0, 1, n).astype(np.float32))
+    few = gpu_occ(np.ascontiguousarray(h[:, :M]), np.r_[wb[:M], wb[-1:]], ell)
+    many = gpu_occ(h, wb, ell)
+    rel = (M + 70) * 2.0 ** -23
+    w = float(np.abs(wb).sum())
+    # |phi d| / l <= exp(-1/2) per feature
+    tol = dict(s=rel * w, c=rel * w, g=rel * w / ell, x=3 * 0.01 * rel * w / ell + 2.0 ** -21 * b, w=rel)
+    a, r = ([*P.occupancy_eval(o, x), P.occupancy_grad(o, x)[1], P.morph_samples(o, x, 3, 0.01),
+             P.occupancy_bwd(o, x, up)] for o in (few, many))
+    for k, u, v in zip("csgx", a, r):
+        assert float((u.double() - v.double()).abs().max()) <= tol[k], k
+    assert float((a[4][1] - r[4][1]).abs().max()) <= tol["g"] * float(up.abs().max())
+    gw = r[4][0][torch.tensor([*range(M), 700], device="cuda")]
+    assert float((a[4][0] - gw).abs().max()) <= 70 * 2.0 ** -23 * float(up.abs().sum())

@@ -90,3 +90,41 @@ print(json.dumps([launches("pdmp_occupancy_bwd", occ(2, 20000), ptr, 1365 * 4 * 
     rbf = [l for l in ls if names([l]) == ["k_rbf"]]
     chunks = -(-1365 * 60 // rbf[0]["grid"][1])
     assert rbf[0]["lds"] >= chunks * 48, rbf
+
+def test_pairwise_lanes_at_the_sizes_that_lost(fake_hip):
+    """The lanes per sample and threads per block where a general rule for few samples or many
+    hinges loses: hinges past one tile (each block restages them in every step), fewer
+    hinges than lanes, blocks that end on a nearly empty round."""
+    cases = [  # dim, M, n, steps (0: values), lanes, threads
+        (2, 6000, 5000, 4, 64, 512), (2, 12000, 26000, 4, 16, 512), (2, 30, 5000, 4, 8, 256),
+        (3, 30, 131072, 0, 1, 256), (2, 4, 600, 4, 1, 256), (2, 2000, 26000, 0, 16, 256),
+        (2, 1000, 26000, 4, 16, 256), (2, 2000, 14000, 0, 16, 512)]
+    out = run(fake_hip, f"""
+print(json.dumps([launches("pdmp_morph_samples", occ(d, M), None, ptr, ptr, n, T, 0.1, None) if T else
+                  launches("pdmp_occupancy_eval", occ(d, M), ptr, n, ptr, ptr, None)
+                  for d, M, n, T, _, _ in {cases}]))
+""")
+    for (d, M, n, T, lanes, threads), (l,) in zip(cases, out):
+        assert l["block"] == threads and l["kernel"].startswith(f"void pdmp::k_rbf<{d}, 1, {lanes}, {threads},"), l
+    (ls,) = run(fake_hip, """
+ws = lib.pdmp_bwd_workspace_size(3, 1000, 200000)
+print(json.dumps([launches("pdmp_occupancy_bwd", occ(3, 1000), ptr, 200000, ptr, None, ptr, None, ptr, ws,
+                           None)]))
+""")
+    assert ls[0]["kernel"].startswith("void pdmp::k_rbf<3, 1, 1, 256,")  # one hinge per lane
+
+
+def test_arm_batches_take_the_kernel_of_their_size(fake_hip):
+    """One link per wave only where its rounds of 1,024 configurations are the shorter."""
+    cases = [(1, 16, 10, "k_arm_grid3d"), (2, 1000, 10, "k_arm_wide"), (2, 3000, 10, "k_arm_grid3d"),
+             (7, 3000, 1, "k_arm_grid3d"), (7, 3000, 10, "k_arm_wide"), (7, 4000, 10, "k_arm_grid3d")]
+    out = run(fake_hip, f"""
+def arm(n):
+    a = _lib.pdmp_arm()
+    a.n_dof, a.pts_per_link = n, 8
+    return C.byref(a)
+print(json.dumps([launches("pdmp_morph_samples", occ(3, 4096, (16, 16, 16)), arm(d), ptr, ptr, n, T, 0.1, None)
+                  for d, n, T, _ in {cases}]))
+""")
+    for (d, n, T, kernel), ls in zip(cases, out):
+        assert names(ls)[-1] == kernel, (d, n, T, names(ls))
