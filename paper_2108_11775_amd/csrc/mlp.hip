@@ -141,7 +141,9 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
     const bool a_k = g.a_sk == 1 && (g.a_sm & 7) == 0 && ((uintptr_t)g.A & 15) == 0;
     const bool b_k = g.b_sk == 1 && (g.b_sn & 7) == 0 && ((uintptr_t)g.B & 15) == 0;
     const bool b_r = g.b_sn == 1 && (g.b_sk & 7) == 0 && ((uintptr_t)g.B & 15) == 0;
-    for (int k0 = 0; k0 < g.K; k0 += kGK) {
+    for (int kt = 0; kt < g.K; kt += kGK) {
+        int k0 = kt;  // opaque: the staging's addresses formed anew, not kept in 28 registers
+        asm volatile("" : "+s"(k0));
         stage_tile(g.A, g.a_sm, g.a_sk, g.M, m0, k0, g.K, a_k, false, lrow, lseg, kr, rseg, As);
         stage_tile(g.B, g.b_sn, g.b_sk, g.N, n0, k0, g.K, b_k, b_r, lrow, lseg, kr, rseg, Bs);
         __syncthreads();

@@ -2,6 +2,7 @@
 against tests/fake_hip.cpp, which records the launches and has no device."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -128,3 +129,24 @@ print(json.dumps([launches("pdmp_morph_samples", occ(3, 4096, (16, 16, 16)), arm
 """)
     for (d, n, T, kernel), ls in zip(cases, out):
         assert names(ls)[-1] == kernel, (d, n, T, names(ls))
+
+
+def test_layered_products_keep_their_waves():
+    """The tiled GEMM of the widths without a fused kernel lives off eight waves per SIMD: at
+    most 64 registers (5 waves: 20 to 30 % slower forwards from 65,536 samples on)."""
+    readelf = "/opt/rocm/llvm/bin/llvm-readelf"
+    if not os.path.exists(readelf):
+        pytest.skip("no llvm-readelf")
+    from paper_2108_11775_amd import _lib
+    data = open(_lib.LIB_PATH, "rb").read()
+    found, at = [], data.find(b"\x7fELF", 1)
+    while at >= 0:
+        if data[at + 18:at + 20] == b"\xe0\x00":  # EM_AMDGPU
+            r = subprocess.run([readelf, "--notes", "-"], input=data[at:], capture_output=True)
+            text = r.stdout.decode(errors="replace")
+            for k in re.split(r"\n\s+- \.agpr_count", text):
+                m = re.search(r"\.name:\s+(\S*k_gemm\S*)", k)
+                if m:
+                    found.append((m[1], int(re.search(r"\.vgpr_count:\s+(\d+)", k)[1])))
+        at = data.find(b"\x7fELF", at + 4)
+    assert len(found) == 3 and all(v <= 64 for _, v in found), found
