@@ -59,6 +59,19 @@ __device__ __forceinline__ float silu_grad_f(float z) {
     return c + z * sp;  // sigma (1 + z (1 - sigma))
 }
 
+// 16 bytes of the caller's memory, which is aligned to its elements only (activations and
+// workspaces to 4 bytes, parameters to 2; still one access each).
+template <class V, class E>
+__device__ __forceinline__ V load16(const E *p) {
+    V v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+template <class V, class E>
+__device__ __forceinline__ void store16(E *p, const V &v) {
+    __builtin_memcpy(p, &v, 16);
+}
+
 enum GemmEpi { kEpiHidden = 1, kEpiOut = 2, kEpiDSilu = 3 };
 
 struct GemmArgs {
@@ -406,16 +419,15 @@ k_mlp_fused(const uint16_t *__restrict__ wbf, const float *__restrict__ par, int
                     const float4 z = make_float4(acc[t][v0] + b4.x, acc[t][v0 + 1] + b4.y,
                                                  acc[t][v0 + 2] + b4.z, acc[t][v0 + 3] + b4.w);
                     if (TRAIN)
-                        *reinterpret_cast<float4 *>(acts.z[l] + ((n >> 5) * TH + t) * 1024 +
-                                                    (v0 >> 2) * 256 + lane * 4) = z;
+                        store16(acts.z[l] + ((n >> 5) * TH + t) * 1024 + (v0 >> 2) * 256 + lane * 4,
+                                z);
                     quad[g] = make_uint2(pack_bf16(silu_f(z.x), silu_f(z.y)),
                                          pack_bf16(silu_f(z.z), silu_f(z.w)));
                 }
                 uint4 w = make_uint4(quad[0].x, quad[0].y, quad[1].x, quad[1].y);
                 if (TRAIN) {
                     w = natural_order(quad[0], quad[1]);
-                    *reinterpret_cast<uint4 *>(acts.h[l] + ((n >> 5) * KH + 2 * t + u8) * 512 +
-                                               lane * 8) = w;
+                    store16(acts.h[l] + ((n >> 5) * KH + 2 * t + u8) * 512 + lane * 8, w);
                 }
                 __builtin_memcpy(&hb[2 * t + u8], &w, 16);
             }
@@ -540,10 +552,7 @@ k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *_
     const int64_t n = (int64_t)blockIdx.x * (kMlpFB / 2) + wv * 32 + r;
     const int64_t nc = n < B ? n : B - 1;
     bf16x8_t dz[KH], nd[KH];
-    {
-        const uint4 v = *reinterpret_cast<const uint4 *>(dF + nc * kIoLd + 8 * hh);
-        __builtin_memcpy(&dz[0], &v, 16);
-    }
+    dz[0] = load16<bf16x8_t>(dF + nc * kIoLd + 8 * hh);
     const int64_t w1 = (int64_t)H * n_in + H;
     // stage rows [0, rows) of columns [0, 8 c8) of W, every load of a batch in flight
     auto stage = [&](const uint16_t *__restrict__ W, int rows, auto c8) {
@@ -587,7 +596,7 @@ k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *_
             auto load_z = [&](float4(&d)[4], int t) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    d[v] = *reinterpret_cast<const float4 *>(zl + t * 1024 + v * 256);
+                    d[v] = load16<float4>(zl + t * 1024 + v * 256);
             };
             load_z(zn, t0);
             if (last) {
@@ -621,7 +630,7 @@ k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *_
                                                        acc[t][v0 + 3] * silu_grad_f(zz.w)));
                     }
                     const uint4 w = natural_order(quad[0], quad[1]);
-                    *reinterpret_cast<uint4 *>(dl + (2 * (t0 + t) + u8) * 512) = w;
+                    store16(dl + (2 * (t0 + t) + u8) * 512, w);
                     __builtin_memcpy(&nd[2 * (t0 + t) + u8], &w, 16);
                 }
             }
@@ -698,8 +707,8 @@ k_mlp_wgrad(MlpWg g, int64_t B, int64_t per, int64_t np, float *__restrict__ par
     auto load = [&](u32x4(&z)[4], u32x4(&h)[4]) {  // the arrays hold whole blocks of 128 rows
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            z[u] = *reinterpret_cast<const u32x4 *>(pz + (u >> 1) * rz + (u & 1) * cz);
-            h[u] = *reinterpret_cast<const u32x4 *>(ph + (u >> 1) * rh + (u & 1) * ch);
+            z[u] = load16<u32x4>(pz + (u >> 1) * rz + (u & 1) * cz);
+            h[u] = load16<u32x4>(ph + (u >> 1) * rh + (u & 1) * ch);
         }
         pz += sz;
         ph += sh;

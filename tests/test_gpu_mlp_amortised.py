@@ -409,3 +409,42 @@ def test_mse_gradient_shapes(n_in, hidden, n_hidden, B):
             a, b = grad[off:off + n_el], gref[off:off + n_el]
             assert np.linalg.norm(a - b) <= tol * np.linalg.norm(b) + 1e-12, (li, n_el)
             off += n_el
+
+
+def _mse_step(mlp, q, t, acts, ws=None, **kw):
+    qh = mlp.forward(q, acts=acts)
+    return [host(v) for v in (qh, *mlp.backward(qh, t, acts, ws=ws, **kw))]
+
+
+@pytest.mark.parametrize("n_in,hidden,n_hidden,B", [(7, 32, 2, 130), (7, 256, 3, 1025), (16, 9, 2, 64),
+                                                    (7, 100, 3, 515), (5, 288, 2, 4097)])
+def test_mlp_buffers_of_any_4_byte_alignment(n_in, hidden, n_hidden, B):
+    """Activations, workspace, parameters and batch at odd 4-byte addresses, the BF16 weights at an
+    odd 2-byte one: the same bits."""
+    require_gpu()
+    import ctypes as C
+    import torch
+    from paper_2108_11775_amd import _lib
+    widths = (n_in,) + (hidden,) * n_hidden + (n_in,)
+    mlp = P.Mlp.from_layers(_net(widths, seed=hidden))
+    rng = np.random.default_rng(B)
+    q, t = (dev(rng.uniform(-3, 3, (n_in, B)).astype(np.float32)) for _ in range(2))
+    ref = _mse_step(mlp, q, t, mlp.acts_buffer(B))
+    inf = host(mlp.forward(q))
+
+    def odd(v, k):  # a copy of v, k bytes past an aligned address
+        b = torch.empty(v.numel() * v.element_size() + 16, dtype=torch.uint8, device="cuda")
+        w = b[k:k + v.numel() * v.element_size()].view(v.dtype).view(v.shape)
+        assert w.data_ptr() % 16 == k
+        return w.copy_(v)
+
+    m = mlp.c_struct()
+    ws = _lib.load().pdmp_mlp_workspace_size(C.byref(m), B)
+    acts = odd(mlp.acts_buffer(B), 4)
+    mlp.params, mlp.params_bf16 = odd(mlp.params, 12), odd(mlp.params_bf16, 2)
+    got = _mse_step(mlp, odd(q, 4), odd(t, 8), acts, ws=odd(torch.empty(ws, dtype=torch.uint8, device="cuda"), 4),
+                    grad=odd(torch.empty_like(mlp.params), 4))
+    assert all(np.array_equal(a, b) for a, b in zip(got, ref))
+    # (the fused inference kernel takes aligned weights only: the layers' sums then have another
+    # order of their terms)
+    assert np.abs(host(mlp.forward(odd(q, 4))) - inf).max() <= 2.0 ** -7 * np.abs(inf).max()
