@@ -383,7 +383,12 @@ int64_t pdmp_mlp_num_params(const pdmp_mlp *mlp);
 /* Round params to BF16 (nearest even) into params_bf16 [num_params] (device). */
 int32_t pdmp_mlp_pack(const pdmp_mlp *mlp, uint16_t *params_bf16, void *stream);
 /* Bytes of saved activations for a training forward of B samples, and of the
- * scratch workspace that forward/backward need. */
+ * scratch workspace that forward/backward need.  The workspace's size never decreases in
+ * B: one for the largest batch serves all.  It holds the backward vectors of every hidden
+ * layer; a smaller one is taken down to two layers' vectors, 2,048 samples' partial sums
+ * and the loss's (2 x 2 w B + 4 S w (w + B / (256 S)) + 8192 bytes, w = hidden >= 16, S =
+ * B / 2048 within 1 and 64, each term rounded up to 256), and the backward then goes layer
+ * by layer. */
 size_t pdmp_mlp_acts_size(const pdmp_mlp *mlp, int64_t B);
 size_t pdmp_mlp_workspace_size(const pdmp_mlp *mlp, int64_t B);
 /* q_hat [n_in][B] = q + f(q) for q [n_in][B].  acts (nullable, device,

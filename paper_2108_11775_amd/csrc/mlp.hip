@@ -24,6 +24,7 @@
 // with lane%32 the sample in the block.
 #include "pdmp_common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace pdmp {
@@ -205,14 +206,24 @@ static int32_t launch_gemm(const GemmArgs &g, hipStream_t st) {
 
 constexpr int kIoLd = 16;  // row length of the BF16 input and output-gradient arrays
 
-// q [n_in][B] FP32 (SoA) -> H0 [B][16] BF16, zero past n_in; a thread per row
+// q [n_in][B] FP32 (SoA) -> H0 [B][16] BF16, zero past n_in; a thread per half row
 __global__ void k_q_to_bf16(const float *__restrict__ q, int n_in, int64_t B, uint16_t *h0) {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = 8 * blockIdx.y;
     if (b >= B) return;
-    uint16_t u[kIoLd];
+    uint16_t u[8];
 #pragma unroll
-    for (int i = 0; i < kIoLd; ++i) u[i] = i < n_in ? f32_to_bf16(q[(int64_t)i * B + b]) : (uint16_t)0;
-    __builtin_memcpy(h0 + b * kIoLd, u, sizeof(u));
+    for (int i = 0; i < 8; ++i)
+        u[i] = c + i < n_in ? f32_to_bf16(q[(int64_t)(c + i) * B + b]) : (uint16_t)0;
+    store16(h0 + b * kIoLd + c, u);
+}
+
+// the same, rows of n_in; a thread per entry
+__global__ void k_q_rows(const float *__restrict__ q, int n_in, int64_t B, uint16_t *h0) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= B * n_in) return;
+    const int64_t b = t / n_in;
+    h0[t] = f32_to_bf16(q[(t - b * n_in) * B + b]);
 }
 
 __global__ void k_f32_to_bf16(const float *__restrict__ x, int64_t n, uint16_t *y) {
@@ -527,8 +538,9 @@ __device__ __forceinline__ bf16x8_t tr_frag(const uint16_t *T, int k0, TrOff o) 
 
 // -------------------------------------------------- chain of data gradients ---
 //
-// dZ_{l-1}[b][i] = (sum_o dZ_l[b][o] W_l[o][i]) SiLU'(Z_{l-1}[b][i]) for l = L-1 .. 1 in one
-// kernel, from dF (the output's gradient, rows of 16, zero past n_in).  Blocks and
+// dZ_{l-1}[b][i] = (sum_o dZ_l[b][o] W_l[o][i]) SiLU'(Z_{l-1}[b][i]) for l = hi .. lo (L-1 .. 1,
+// or a layer at a time, where dz[hi] may be dz[hi - 1]: a wave's vectors are read before
+// they are written) in one kernel, from dF (the output's gradient, rows of 16, zero past n_in).  Blocks and
 // accumulator layout as k_mlp_fused (C = W^T dZ^T, a wave its own 32 samples), the
 // contraction in natural order as its training form; W_l is staged row-major in passes of
 // TP column tiles and read transposed.  The vectors go from layer to layer in registers;
@@ -541,8 +553,8 @@ struct MlpChain {
 
 template <int TH>
 __global__ void __launch_bounds__(kMlpFB) __attribute__((amdgpu_waves_per_eu(2)))
-k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *__restrict__ dF,
-            int64_t B, MlpChain ch) {
+k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *dF, int64_t B,
+            MlpChain ch, int hi, int lo) {
     constexpr int H = 32 * TH, KH = 2 * TH;
     constexpr int TP = TH > 4 ? (TH + 1) / 2 : TH, CW = 32 * TP;
     static_assert(CW <= kTrRow, "a pass fits a staged row");
@@ -552,7 +564,13 @@ k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *_
     const int64_t n = (int64_t)blockIdx.x * (kMlpFB / 2) + wv * 32 + r;
     const int64_t nc = n < B ? n : B - 1;
     bf16x8_t dz[KH], nd[KH];
-    dz[0] = load16<bf16x8_t>(dF + nc * kIoLd + 8 * hh);
+    if (hi == L - 1) {
+        dz[0] = load16<bf16x8_t>(dF + nc * kIoLd + 8 * hh);
+    } else {
+#pragma unroll
+        for (int s = 0; s < KH; ++s)
+            dz[s] = load16<bf16x8_t>(ch.dz[hi] + ((n >> 5) * KH + s) * 512 + lane * 8);
+    }
     const int64_t w1 = (int64_t)H * n_in + H;
     // stage rows [0, rows) of columns [0, 8 c8) of W, every load of a batch in flight
     auto stage = [&](const uint16_t *__restrict__ W, int rows, auto c8) {
@@ -569,7 +587,7 @@ k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *_
 #pragma unroll
     for (int t = 0; t < TP; ++t) off[t] = tr_off(32 * t, lane);
 #pragma unroll 1
-    for (int l = L - 1; l >= 1; --l) {
+    for (int l = hi; l >= lo; --l) {
         const bool last = l == L - 1;
         const uint16_t *W = wbf + w1 + (int64_t)(l - 1) * ((int64_t)H * H + H);
         const float *zl = ch.z[l - 1] + (n >> 5) * TH * 1024 + lane * 4;
@@ -704,7 +722,7 @@ k_mlp_wgrad(MlpWg g, int64_t B, int64_t per, int64_t np, float *__restrict__ par
                    : row * ld + c;
     };
     const uint16_t *pz = y.dz + base(zb, ldz, o0), *ph = y.h + base(hb, ldh, i0);
-    auto load = [&](u32x4(&z)[4], u32x4(&h)[4]) {  // the arrays hold whole blocks of 128 rows
+    auto load = [&](u32x4(&z)[4], u32x4(&h)[4]) {  // whole rounds lie inside the arrays
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             z[u] = load16<u32x4>(pz + (u >> 1) * rz + (u & 1) * cz);
@@ -856,10 +874,13 @@ static MlpActs act_ptrs(const MlpLayout &ly, void *acts, int64_t B) {
     return p;
 }
 
-// Inference-only forward keeps two BF16 activation buffers.
-size_t mlp_fwd_ws_bytes(const pdmp_mlp &m, int64_t B) {
-    return al256((size_t)B * kIoLd * 2) + 2 * al256((size_t)B * mlp_ld(m.hidden) * 2);
+// Inference-only forward keeps the BF16 input and two BF16 activation buffers in rows of mlp_ld,
+// whose operands are 16-byte loads; in a smaller workspace rows of H.
+static size_t mlp_fwd_ws(const pdmp_mlp &m, int64_t B, int ld) {
+    return al256((size_t)B * m.n_in * 2) + 2 * al256((size_t)B * ld * 2);
 }
+size_t mlp_fwd_ws_bytes(const pdmp_mlp &m, int64_t B) { return mlp_fwd_ws(m, B, mlp_ld(m.hidden)); }
+size_t mlp_fwd_ws_least(const pdmp_mlp &m, int64_t B) { return mlp_fwd_ws(m, B, m.hidden); }
 
 template <bool TRAIN>
 static int32_t launch_mlp_fused(const pdmp_mlp &m, int L, const float *q, int64_t B, float *qhat,
@@ -880,34 +901,39 @@ static int32_t launch_mlp_fused(const pdmp_mlp &m, int L, const float *q, int64_
 }
 
 int32_t launch_mlp_forward(const pdmp_mlp &m, const float *q, int64_t B, float *qhat, void *acts,
-                           void *ws, hipStream_t st) {
+                           void *ws, size_t ws_bytes, hipStream_t st) {
     const MlpLayout ly = layout_of(m);
     if (mlp_fused_shape(m) && (acts || ((uintptr_t)m.params_bf16 & 15) == 0)) {
         if (!acts) return launch_mlp_fused<false>(m, ly.L, q, B, qhat, MlpActs{}, st);
         return launch_mlp_fused<true>(m, ly.L, q, B, qhat, act_ptrs(ly, acts, B), st);
     }
-    const int ld = mlp_ld(ly.H);
+    const int ld = acts || ws_bytes >= mlp_fwd_ws_bytes(m, B) ? mlp_ld(ly.H) : ly.H;
+    const int ld0 = acts ? kIoLd : ly.n_in;
     MlpActs p{};
     if (acts) {
         p = act_ptrs(ly, acts, B);
+        if (int32_t e = grid_guard((B + 255) / 256, 256, "k_q_to_bf16")) return e;
+        hipLaunchKernelGGL(k_q_to_bf16, dim3((unsigned)((B + 255) / 256), kIoLd / 8), dim3(256), 0, st,
+                           q, ly.n_in, B, p.h0);
+        if (int32_t e = check_launch("k_q_to_bf16")) return e;
     } else {
         char *c = (char *)ws;
         p.h0 = (uint16_t *)c;
-        c += al256((size_t)B * kIoLd * 2);
+        c += al256((size_t)B * ld0 * 2);
         for (int l = 0; l < ly.L - 1; ++l)
             p.h[l] = (uint16_t *)(c + (l & 1) * al256((size_t)B * ld * 2));
+        const int64_t blocks = (B * ly.n_in + 255) / 256;
+        if (int32_t e = grid_guard(blocks, 256, "k_q_rows")) return e;
+        hipLaunchKernelGGL(k_q_rows, dim3((unsigned)blocks), dim3(256), 0, st, q, ly.n_in, B, p.h0);
+        if (int32_t e = check_launch("k_q_rows")) return e;
     }
-    if (int32_t e = grid_guard((B + 255) / 256, 256, "k_q_to_bf16")) return e;
-    hipLaunchKernelGGL(k_q_to_bf16, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, q,
-                       ly.n_in, B, p.h0);
-    if (int32_t e = check_launch("k_q_to_bf16")) return e;
     for (int l = 0; l < ly.L; ++l) {
         GemmArgs g;
         g.M = (int)B;
         g.N = ly.out(l);
         g.K = ly.in(l);
         g.A = l == 0 ? p.h0 : p.h[l - 1];
-        g.a_sm = l == 0 ? kIoLd : ld;
+        g.a_sm = l == 0 ? ld0 : ld;
         g.a_sk = 1;
         g.B = m.params_bf16 + ly.woff(l);
         g.b_sn = ly.in(l);
@@ -930,120 +956,199 @@ int32_t launch_mlp_forward(const pdmp_mlp &m, const float *q, int64_t B, float *
     return PDMP_OK;
 }
 
+// ---- backward: sizes ----
+//
+// With the whole workspace all layers' vectors are kept and all weight gradients are one
+// launch.  In a smaller one the vectors of one layer are kept at a time, in rows of H where the
+// kernels' layouts leave it open, and each layer's weight gradient is a launch of its own:
+// 65,536 x 7-256-256-256-7 in 76 MB instead of 125.
+
+// Ranges of samples of a weight gradient of `tiles` output tiles: each writes a row of partial
+// sums.  At least 256 samples (four rounds) each, and no more ranges (in eights, one per XCD) than
+// fill the 512 block slots once -- but ranges of 2,048 samples and more as far as 64 go, whatever
+// the tiles: one FP32 accumulator sums a range.
+static int64_t wgrad_ranges(int tiles, int64_t B) {
+    int64_t most = kWgSlots / tiles / 8 * 8;
+    most = most < 8 ? 8 : (most > 64 ? 64 : most);
+    const int64_t least = std::min<int64_t>(std::max<int64_t>(B / 2048, 1), 64);
+    return std::max(std::min((B + kWgSamples - 1) / kWgSamples, most), least);
+}
+// Samples per range (whole rounds), and the rows that there are then (wgrad_ranges at most).
+static int64_t wgrad_per(int64_t ranges, int64_t B) {
+    return ((B + ranges - 1) / ranges + kWgK - 1) / kWgK * kWgK;
+}
+static int64_t wgrad_rows(int64_t ranges, int64_t B) {
+    const int64_t per = wgrad_per(ranges, B);
+    return (B + per - 1) / per;
+}
+static int layer_tiles(const MlpLayout &ly, int l) {
+    return (ly.out(l) + kWgT - 1) / kWgT * ((ly.in(l) + kWgT - 1) / kWgT);
+}
 static int wgrad_tiles(const MlpLayout &ly) {
     int t = 0;
-    for (int l = 0; l < ly.L; ++l)
-        t += (ly.out(l) + kWgT - 1) / kWgT * ((ly.in(l) + kWgT - 1) / kWgT);
+    for (int l = 0; l < ly.L; ++l) t += layer_tiles(ly, l);
     return t;
 }
 
-// Samples per partial row of the weight gradients: at least 256 (four rounds), and no more
-// rows (in eights, one per XCD) than fill the 512 block slots once.
-static int64_t wgrad_per(const MlpLayout &ly, int64_t B) {
-    int64_t most = kWgSlots / wgrad_tiles(ly) / 8 * 8;
-    most = most < 8 ? 8 : (most > 64 ? 64 : most);
-    int64_t s = (B + kWgSamples - 1) / kWgSamples;
-    if (s > most) s = most;
-    const int64_t per = (B + s - 1) / s;
-    return (per + kWgK - 1) / kWgK * kWgK;
-}
-static int64_t wgrad_rows(const MlpLayout &ly, int64_t B) {
-    const int64_t per = wgrad_per(ly, B);
-    return (B + per - 1) / per;
+// A backward's workspace: dF, the layers' vectors, partial rows, partial losses.
+struct MlpBwd {
+    bool layered;         // a layer at a time
+    bool one;             // its vectors in one buffer (fused kernels), else two in turn
+    int64_t rows;         // rows of dF and of a buffer
+    int ld, bufs;         // row length and number of the vectors' buffers
+    bool dF_in_buf;       // dF lies in the second buffer
+    int64_t ranges, part; // partial rows and entries of one (no rows: the gradient itself)
+    int nb;               // blocks of the loss
+    size_t bytes;
+};
+
+static MlpBwd mlp_bwd_plan(const pdmp_mlp &m, int64_t B, bool layered) {
+    const MlpLayout ly = layout_of(m);
+    const bool fused = mlp_fused_shape(m);
+    MlpBwd p{};
+    p.layered = layered;
+    p.ld = fused || !layered ? mlp_ld(ly.H) : ly.H;
+    p.one = layered && fused;
+    p.bufs = !layered ? ly.L - 1 : fused ? 1 : 2;
+    p.dF_in_buf = layered && !fused && p.ld >= kIoLd;
+    p.ranges = layered ? std::min<int64_t>(std::max<int64_t>(B / 2048, 1), 64)
+                       : wgrad_ranges(wgrad_tiles(ly), B);
+    // a weight gradient reads whole rounds of rows and eights of columns (and drops what lies past
+    // the batch and the row): past the vectors, where those are rows of the batch alone, into what
+    // follows them
+    p.rows = fused || !layered ? mlp_rows(B) : (p.ranges > 1 ? B : (B + kWgK - 1) / kWgK * kWgK);
+    p.part = ly.nparams();
+    if (layered) {
+        p.part = 0;
+        for (int l = 0; l < ly.L && p.ranges > 1; ++l)
+            p.part = std::max(p.part, (int64_t)ly.out(l) * ly.in(l) + ly.out(l));
+    }
+    p.nb = layered ? (int)std::min<int64_t>(256, (B * kIoLd + 255) / 256) : 1024;
+    p.bytes = (p.dF_in_buf ? 0 : al256((size_t)p.rows * kIoLd * 2)) +
+              p.bufs * al256((size_t)p.rows * p.ld * 2) +
+              std::max(al256((size_t)p.ranges * p.part * 4) + al256(p.nb * sizeof(double)),
+                       p.rows == B ? al256((size_t)kWgK * p.ld * 2 + 16) : 0);
+    return p;
 }
 
-size_t mlp_bwd_ws_bytes(const pdmp_mlp &m, int64_t B) {
-    const MlpLayout ly = layout_of(m);
-    return al256((size_t)mlp_rows(B) * kIoLd * 2) + (ly.L - 1) * al256((size_t)mlp_rows(B) * mlp_ld(ly.H) * 2) +
-           al256((size_t)wgrad_rows(ly, B) * ly.nparams() * 4) + al256(1024 * sizeof(double));
+size_t mlp_bwd_ws_bytes(const pdmp_mlp &m, int64_t B) { return mlp_bwd_plan(m, B, false).bytes; }
+size_t mlp_bwd_ws_least(const pdmp_mlp &m, int64_t B) {
+    return std::min(mlp_bwd_plan(m, B, true).bytes, mlp_bwd_ws_bytes(m, B));
+}
+
+static int32_t launch_mlp_chain(const pdmp_mlp &m, const MlpLayout &ly, const uint16_t *dF, int64_t B,
+                                const MlpChain &ch, int hi, int lo, hipStream_t st) {
+    const int64_t blocks = (B + kMlpFB / 2 - 1) / (kMlpFB / 2);
+    if (int32_t e = grid_guard(blocks, kMlpFB, "k_mlp_chain")) return e;
+    switch (ly.H / 32) {
+#define PDMP_CHAIN(TH)                                                                        \
+    case TH:                                                                                  \
+        hipLaunchKernelGGL(k_mlp_chain<TH>, dim3((unsigned)blocks), dim3(kMlpFB), 0, st,      \
+                           m.params_bf16, ly.n_in, ly.L, dF, B, ch, hi, lo);                  \
+        break;
+        PDMP_CHAIN(1) PDMP_CHAIN(2) PDMP_CHAIN(3) PDMP_CHAIN(4)
+        PDMP_CHAIN(5) PDMP_CHAIN(6) PDMP_CHAIN(7) PDMP_CHAIN(8)
+#undef PDMP_CHAIN
+    }
+    return check_launch("k_mlp_chain");
 }
 
 // Backward of the MSE loss through the whole network from saved activations.
 // grad: FP32 [nparams] in the flat layout; loss (nullable): device [1].
 int32_t launch_mlp_backward(const pdmp_mlp &m, const float *qhat, const float *target, int64_t B,
-                            void *acts, float *grad, float *loss, void *ws, hipStream_t st,
-                            const uint8_t *hard, float hard_w) {
+                            void *acts, float *grad, float *loss, void *ws, size_t ws_bytes,
+                            hipStream_t st, const uint8_t *hard, float hard_w) {
     const MlpLayout ly = layout_of(m);
     const MlpActs ap = act_ptrs(ly, acts, B);
-    const int ld = mlp_ld(ly.H);
-    const int64_t S = wgrad_rows(ly, B), np = ly.nparams();
+    const bool fused = mlp_fused_shape(m);
+    const MlpBwd pl = mlp_bwd_plan(m, B, ws_bytes < mlp_bwd_ws_bytes(m, B));
     char *c = (char *)ws;
     uint16_t *dF = (uint16_t *)c;
-    c += al256((size_t)mlp_rows(B) * kIoLd * 2);
+    if (!pl.dF_in_buf) c += al256((size_t)pl.rows * kIoLd * 2);
+    const size_t buf = al256((size_t)pl.rows * pl.ld * 2);
     MlpChain ch{};
     for (int l = 0; l < ly.L - 1; ++l) {
         ch.z[l] = ap.z[l];
-        ch.dz[l] = (uint16_t *)c;
-        c += al256((size_t)mlp_rows(B) * ld * 2);
+        // layer by layer in two buffers: the last hidden layer's vectors in the first, dF, which
+        // they are formed from, in the second
+        ch.dz[l] = (uint16_t *)(c + (!pl.layered ? l : pl.one ? 0 : (ly.L - l) & 1) * buf);
     }
+    if (pl.dF_in_buf) dF = (uint16_t *)(c + buf);
+    c += pl.bufs * buf;
     float *part = (float *)c;
-    c += al256((size_t)S * np * 4);
+    c += al256((size_t)pl.ranges * pl.part * 4);
     double *rparts = (double *)c;
+    const double scale = 1.0 / ((double)ly.n_in * (double)B);
 
-    const int nb = 1024;
-    hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, st, qhat, target, ly.n_in, B,
-                       (float)(1.0 / ((double)ly.n_in * (double)B)), hard, hard_w, dF, rparts);
+    hipLaunchKernelGGL(k_mse, dim3(pl.nb), dim3(256), 0, st, qhat, target, ly.n_in, B, (float)scale,
+                       hard, hard_w, dF, rparts);
     if (int32_t e = check_launch("k_mse")) return e;
 
-    const bool fused = mlp_fused_shape(m);
-    if (fused) {
-        const int64_t blocks = (B + kMlpFB / 2 - 1) / (kMlpFB / 2);
-        if (int32_t e = grid_guard(blocks, kMlpFB, "k_mlp_chain")) return e;
-        switch (ly.H / 32) {
-#define PDMP_CHAIN(TH)                                                                        \
-    case TH:                                                                                  \
-        hipLaunchKernelGGL(k_mlp_chain<TH>, dim3((unsigned)blocks), dim3(kMlpFB), 0, st,      \
-                           m.params_bf16, ly.n_in, ly.L, dF, B, ch);                          \
-        break;
-            PDMP_CHAIN(1) PDMP_CHAIN(2) PDMP_CHAIN(3) PDMP_CHAIN(4)
-            PDMP_CHAIN(5) PDMP_CHAIN(6) PDMP_CHAIN(7) PDMP_CHAIN(8)
-#undef PDMP_CHAIN
-        }
-        if (int32_t e = check_launch("k_mlp_chain")) return e;
-    } else {
-        for (int l = ly.L - 1; l >= 1; --l) {
-            // dZ_{l-1}[b][i] = (sum_o dZ[b][o] W_l[o][i]) * SiLU'(Z_{l-1}[b][i])
+    // dZ_{l-1}[b][i] = (sum_o dZ[b][o] W_l[o][i]) * SiLU'(Z_{l-1}[b][i]) for l = hi .. lo
+    auto data_grad = [&](int hi, int lo) -> int32_t {
+        if (fused) return launch_mlp_chain(m, ly, dF, B, ch, hi, lo, st);
+        for (int l = hi; l >= lo; --l) {
             GemmArgs gd;
             gd.M = (int)B;
             gd.N = ly.in(l);
             gd.K = ly.out(l);
             gd.A = l == ly.L - 1 ? dF : ch.dz[l];
-            gd.a_sm = l == ly.L - 1 ? kIoLd : ld;
+            gd.a_sm = l == ly.L - 1 ? kIoLd : pl.ld;
             gd.a_sk = 1;
             gd.B = m.params_bf16 + ly.woff(l);
             gd.b_sn = 1;
             gd.b_sk = ly.in(l);
             gd.hout = ch.dz[l - 1];
-            gd.ldh = ld;
+            gd.ldh = pl.ld;
             gd.zprev = ap.z[l - 1];
             if (int32_t e = launch_gemm<kEpiDSilu>(gd, st)) return e;
         }
+        return PDMP_OK;
+    };
+    // The gradients of layers [lo, hi] into grad from its entry woff(lo) on: by partial rows of
+    // np entries, or, of one range, at once.
+    auto weight_grad = [&](int lo, int hi, int64_t np, float *loss) -> int32_t {
+        MlpWg wg{};
+        const int64_t base = ly.woff(lo);
+        for (int l = lo; l <= hi; ++l) {
+            MlpWgLayer &y = wg.layer[wg.L++];
+            const bool last = l == ly.L - 1;
+            y.dz = last ? dF : ch.dz[l];
+            y.ldz = last ? kIoLd : pl.ld;
+            y.h = l == 0 ? ap.h0 : ap.h[l - 1];
+            y.ldh = l == 0 ? kIoLd : mlp_ld(ly.H);
+            y.zblk = !last && fused;
+            y.hblk = l > 0 && fused;
+            y.O = ly.out(l);
+            y.I = ly.in(l);
+            y.woff = ly.woff(l) - base;
+            y.boff = ly.boff(l) - base;
+            y.tile0 = wg.tiles;
+            y.tiles_i = (y.I + kWgT - 1) / kWgT;
+            wg.tiles += layer_tiles(ly, l);
+        }
+        const int64_t per = wgrad_per(pl.ranges, B), S = wgrad_rows(pl.ranges, B);
+        hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(wg.tiles * ((S + 7) / 8 * 8))), dim3(256), 0,
+                           st, wg, B, per, np, pl.part ? part : grad + base);
+        const int64_t sum = pl.part ? np : 0;
+        if (sum || loss)
+            hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((sum + 255) / 256 + (loss ? 1 : 0))),
+                               dim3(256), 0, st, part, (int)S, sum, grad + base, rparts, pl.nb, scale,
+                               loss);
+        return check_launch("mlp wgrad");
+    };
+    if (!pl.layered) {
+        if (int32_t e = data_grad(ly.L - 1, 1)) return e;
+        return weight_grad(0, ly.L - 1, ly.nparams(), loss);
     }
-    MlpWg wg{};
-    wg.L = ly.L;
-    for (int l = 0; l < ly.L; ++l) {
-        MlpWgLayer &y = wg.layer[l];
-        const bool last = l == ly.L - 1;
-        y.dz = last ? dF : ch.dz[l];
-        y.ldz = last ? kIoLd : ld;
-        y.h = l == 0 ? ap.h0 : ap.h[l - 1];
-        y.ldh = l == 0 ? kIoLd : ld;
-        y.zblk = !last && fused;
-        y.hblk = l > 0 && fused;
-        y.O = ly.out(l);
-        y.I = ly.in(l);
-        y.woff = ly.woff(l);
-        y.boff = ly.boff(l);
-        y.tile0 = wg.tiles;
-        y.tiles_i = (y.I + kWgT - 1) / kWgT;
-        wg.tiles += (y.O + kWgT - 1) / kWgT * y.tiles_i;
+    for (int l = ly.L - 1; l >= 0; --l) {
+        if (int32_t e = weight_grad(l, l, (int64_t)ly.out(l) * ly.in(l) + ly.out(l),
+                                    l == 0 ? loss : nullptr))
+            return e;
+        if (l > 0)
+            if (int32_t e = data_grad(l, l)) return e;
     }
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(wg.tiles * ((S + 7) / 8 * 8))), dim3(256), 0, st, wg, B, wgrad_per(ly, B),
-                       np, part);
-    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((np + 255) / 256 + (loss ? 1 : 0))), dim3(256),
-                       0, st, part, (int)S, np, grad, rparts, nb,
-                       1.0 / ((double)ly.n_in * (double)B), loss);
-    return check_launch("mlp wgrad");
+    return PDMP_OK;
 }
 
 int32_t launch_f32_to_bf16(const float *x, int64_t n, uint16_t *y, hipStream_t st) {

@@ -658,13 +658,13 @@ int32_t pdmp_mlp_forward(const pdmp_mlp *mlp, const float *q, int64_t B, float *
     PDMP_REQUIRE(q && q_hat, "q/q_hat NULL");
     PDMP_REQUIRE(B <= 0x7fffffff, "B too large");
     if (!acts) {
-        const size_t need = mlp_fwd_ws_bytes(*mlp, B);
+        const size_t need = mlp_fwd_ws_least(*mlp, B);
         if (!ws || ws_bytes < need) {
             set_error("workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : (size_t)0);
             return PDMP_ENOMEM;
         }
     }
-    return launch_mlp_forward(*mlp, q, B, q_hat, acts, ws, (hipStream_t)stream);
+    return launch_mlp_forward(*mlp, q, B, q_hat, acts, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int32_t pdmp_mlp_backward(const pdmp_mlp *mlp, const float *q_hat, const float *target,
@@ -674,12 +674,13 @@ int32_t pdmp_mlp_backward(const pdmp_mlp *mlp, const float *q_hat, const float *
     if (st) return st;
     PDMP_REQUIRE(B >= 1 && B <= 0x7fffffff, "B out of range");
     PDMP_REQUIRE(q_hat && target && acts && grad, "NULL argument");
-    const size_t need = mlp_bwd_ws_bytes(*mlp, B);
+    const size_t need = mlp_bwd_ws_least(*mlp, B);
     if (!ws || ws_bytes < need) {
         set_error("workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : (size_t)0);
         return PDMP_ENOMEM;
     }
-    return launch_mlp_backward(*mlp, q_hat, target, B, acts, grad, loss, ws, (hipStream_t)stream);
+    return launch_mlp_backward(*mlp, q_hat, target, B, acts, grad, loss, ws, ws_bytes,
+                               (hipStream_t)stream);
 }
 
 int32_t pdmp_mlp_backward_weighted(const pdmp_mlp *mlp, const float *q_hat, const float *target,
@@ -691,13 +692,13 @@ int32_t pdmp_mlp_backward_weighted(const pdmp_mlp *mlp, const float *q_hat, cons
     PDMP_REQUIRE(B >= 1 && B <= 0x7fffffff, "B out of range");
     PDMP_REQUIRE(q_hat && target && acts && grad, "NULL argument");
     PDMP_REQUIRE(hard_weight >= 0.0f && hard_weight < INFINITY, "hard_weight not finite and >= 0");
-    const size_t need = mlp_bwd_ws_bytes(*mlp, B);
+    const size_t need = mlp_bwd_ws_least(*mlp, B);
     if (!ws || ws_bytes < need) {
         set_error("workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : (size_t)0);
         return PDMP_ENOMEM;
     }
-    return launch_mlp_backward(*mlp, q_hat, target, B, acts, grad, loss, ws, (hipStream_t)stream,
-                               hard, hard_weight);
+    return launch_mlp_backward(*mlp, q_hat, target, B, acts, grad, loss, ws, ws_bytes,
+                               (hipStream_t)stream, hard, hard_weight);
 }
 
 int32_t pdmp_arm_max_occupancy(const pdmp_occupancy *occ, const pdmp_arm *arm, const float *q,
@@ -726,12 +727,17 @@ int32_t pdmp_arm_max_occupancy(const pdmp_occupancy *occ, const pdmp_arm *arm, c
 
 static size_t al256h(size_t b) { return (b + 255) & ~(size_t)255; }
 
-size_t pdmp_amortised_workspace_size(const pdmp_mlp *mlp, const pdmp_arm *arm, int64_t n) {
-    if (check_mlp(mlp, false) || !arm || n < 1) return 0;
+// Beside the network's part.
+static size_t amortised_rest(const pdmp_arm *arm, int64_t n) {
     const size_t nb = (size_t)((n + 255) / 256);
-    return mlp_fwd_ws_bytes(*mlp, n) + al256h((size_t)n) /* flags */ +
+    return al256h((size_t)n) /* flags */ +
            2 * al256h(nb * 4) + al256h(8) + al256h((size_t)n * 4) /* idx */ +
            al256h((size_t)arm->n_dof * n * 4) /* compact batch */;
+}
+
+size_t pdmp_amortised_workspace_size(const pdmp_mlp *mlp, const pdmp_arm *arm, int64_t n) {
+    if (check_mlp(mlp, false) || !arm || n < 1) return 0;
+    return mlp_fwd_ws_bytes(*mlp, n) + amortised_rest(arm, n);
 }
 
 // from_qhat: the fallback gathers the flagged rows of q_hat (out) instead of q.
@@ -751,7 +757,7 @@ static int32_t amortised_impl(const pdmp_mlp *mlp, const pdmp_occupancy *occ, co
     PDMP_REQUIRE(T >= 0 && std::isfinite(eta) && std::isfinite(thresh), "bad T/eta/thresh");
     if (n == 0) return PDMP_OK;
     PDMP_REQUIRE(q && out && q != out, "q/out NULL or aliased");
-    const size_t need = pdmp_amortised_workspace_size(mlp, arm, n);
+    const size_t rest = amortised_rest(arm, n), need = mlp_fwd_ws_least(*mlp, n) + rest;
     if (!ws || ws_bytes < need) {
         set_error("workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : (size_t)0);
         return PDMP_ENOMEM;
@@ -760,7 +766,9 @@ static int32_t amortised_impl(const pdmp_mlp *mlp, const pdmp_occupancy *occ, co
     const size_t nb = (size_t)((n + 255) / 256);
     char *c = (char *)ws;
     void *mws = c;
-    c += mlp_fwd_ws_bytes(*mlp, n);
+    const size_t mws_bytes =
+        ws_bytes - rest < mlp_fwd_ws_bytes(*mlp, n) ? need - rest : mlp_fwd_ws_bytes(*mlp, n);
+    c += mws_bytes;
     uint8_t *fl = flag ? flag : (uint8_t *)c;
     c += al256h((size_t)n);
     uint32_t *counts = (uint32_t *)c;
@@ -777,7 +785,7 @@ static int32_t amortised_impl(const pdmp_mlp *mlp, const pdmp_occupancy *occ, co
     derive_scales(occ->lengthscale, kappa, gscale);
     const int *grid = has_grid(occ) ? occ->grid : nullptr;
     if ((st = grid_check(occ, stream))) return st;
-    if ((st = launch_mlp_forward(*mlp, q, n, out, nullptr, mws, s))) return st;
+    if ((st = launch_mlp_forward(*mlp, q, n, out, nullptr, mws, mws_bytes, s))) return st;
     st = PDMP_EUNSUPPORTED;
     if (grid)
         st = launch_arm_grid3d(*arm, occ->hinges, occ->weights, occ->n_hinges, grid, kappa, gscale,

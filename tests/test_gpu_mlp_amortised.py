@@ -448,3 +448,79 @@ def test_mlp_buffers_of_any_4_byte_alignment(n_in, hidden, n_hidden, B):
     # (the fused inference kernel takes aligned weights only: the layers' sums then have another
     # order of their terms)
     assert np.abs(host(mlp.forward(odd(q, 4))) - inf).max() <= 2.0 ** -7 * np.abs(inf).max()
+
+
+@pytest.mark.parametrize("n_in,hidden,n_hidden,B", [
+    (7, 32, 1, 1), (7, 32, 3, 129), (6, 96, 2, 700), (7, 256, 3, 9000), (7, 16, 2, 300), (7, 33, 2, 1000),
+    (7, 100, 3, 4097), (7, 101, 1, 8193), (5, 300, 2, 6000), (7, 600, 2, 5000), (1, 1001, 1, 4200)])
+def test_mlp_in_the_least_workspace(n_in, hidden, n_hidden, B):
+    """A workspace of two layers' vectors: the backward goes layer by layer and sums other ranges of
+    samples (an FP32 sum of the same products, 2^-24 per product's accumulation: within 1e-5 of the
+    norm), the layered inference takes rows of the widths themselves (the same sums)."""
+    require_gpu()
+    import ctypes as C
+    import torch
+    from paper_2108_11775_amd import _lib
+    widths = (n_in,) + (hidden,) * n_hidden + (n_in,)
+    mlp = P.Mlp.from_layers(_net(widths, seed=hidden + B))
+    rng = np.random.default_rng(B)
+    q, t = (dev(rng.uniform(-3, 3, (n_in, B)).astype(np.float32)) for _ in range(2))
+    hard = dev((rng.uniform(size=B) < 0.3).astype(np.uint8))
+    acts = mlp.acts_buffer(B)
+    al = lambda b: (b + 255) // 256 * 256
+    w, S = max(hidden, n_in), min(max(B // 2048, 1), 64)
+    least = 2 * al(2 * B * w) + al(4 * S * w * w) + al(4 * w * (-(-B // 256))) + al(8192)
+    assert least < _lib.load().pdmp_mlp_workspace_size(C.byref(mlp.c_struct()), B) or n_hidden < 3
+    ref = _mse_step(mlp, q, t, acts, hard=hard, hard_weight=3.0)
+    ws = torch.full((least,), 0xff, dtype=torch.uint8, device="cuda")  # NaN everywhere
+    got = _mse_step(mlp, q, t, acts, ws=ws, hard=hard, hard_weight=3.0)
+    assert np.array_equal(got[0], ref[0])
+    assert abs(got[1][0] - ref[1][0]) <= 1e-6 * abs(ref[1][0])
+    off = 0
+    for fi, fo in zip(widths, widths[1:]):
+        for k in (fi * fo, fo):
+            a, b = got[2][off:off + k], ref[2][off:off + k]
+            assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), (fi, fo, k)
+            off += k
+    fwd = al(2 * B * n_in) + 2 * al(2 * B * hidden)
+    wsf, out = torch.full((fwd,), 0xff, dtype=torch.uint8, device="cuda"), torch.empty_like(q)
+    m = mlp.c_struct()
+    _lib.call("pdmp_mlp_forward", C.byref(m), q.data_ptr(), B, out.data_ptr(), None, wsf.data_ptr(), fwd, None)
+    assert np.array_equal(host(out), host(mlp.forward(q)))
+
+
+@pytest.mark.parametrize("n_in,hidden,n_hidden,B", [
+    (7, 32, 1, 129), (7, 256, 3, 1025), (7, 192, 1, 2500), (7, 288, 1, 4097), (7, 100, 2, 515),
+    (6, 128, 2, 20001), (7, 256, 6, 17000), (7, 600, 1, 4100)])
+def test_mse_gradient_edges_of_blocks_and_ranges(n_in, hidden, n_hidden, B):
+    """The samples on either side of every edge (a round of 64, a block of 128, a range, the batch's
+    end) carry all but 1e-3 of the gradient, so that one left out or taken twice shows: each alone
+    is a twentieth or more of it, ten times the BF16 tolerance of test_mse_gradient_shapes."""
+    require_gpu()
+    widths = (n_in,) + (hidden,) * n_hidden + (n_in,)
+    layers = _net(widths, seed=hidden + B)
+    mlp = P.Mlp.from_layers(layers)
+    rng = np.random.default_rng(B)
+    q = rng.uniform(-math.pi, math.pi, (n_in, B)).astype(np.float32)
+    t = q + 0.3 * rng.normal(size=q.shape).astype(np.float32)
+    per = 64 * np.array([-(-B // r) // 64 + (-(-B // r) % 64 > 0) for r in (2, 8, 16, 40)])
+    edges = np.r_[0, 63, 64, 127, 128, per - 1, per, 2 * per, B - B % 64 - 1, B - B % 64, B - 2, B - 1]
+    edges = np.unique(edges[(edges >= 0) & (edges < B)])
+    tol = (2 * (n_hidden + 1) + 2) * 2.0 ** -9
+    for k in range(0, len(edges), 4):  # four at a time
+        hard = np.zeros(B, np.uint8)
+        hard[edges[k:k + 4]] = 1
+        weight = float(1e4 * B)
+        acts = mlp.acts_buffer(B)
+        qh = mlp.forward(dev(q), acts=acts)
+        _, grad = mlp.backward(qh, dev(t), acts, hard=dev(hard), hard_weight=weight)
+        sel = np.flatnonzero(hard)
+        _, gref = O.mlp_loss_grad(widths, O.mlp_pack([(_bf16(W), b) for W, b in layers]),
+                                  np.ascontiguousarray(q[:, sel]), np.ascontiguousarray(t[:, sel]))
+        gref = gref * weight * len(sel) / B
+        off, grad = 0, host(grad)
+        for fi, fo in zip(widths, widths[1:]):
+            for n_el in (fi * fo, fo):
+                a, b = grad[off:off + n_el], gref[off:off + n_el]
+                assert np.linalg.norm(a - b) <= (tol + 1e-3) * np.linalg.norm(b), (sel, fi, fo, n_el)
+                off += n_el

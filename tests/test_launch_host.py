@@ -131,6 +131,82 @@ print(json.dumps([launches("pdmp_morph_samples", occ(3, 4096, (16, 16, 16)), arm
         assert names(ls)[-1] == kernel, (d, n, T, names(ls))
 
 
+MLP = """
+def mlp(n_in, H, L):
+    return C.byref(_lib.pdmp_mlp(n_in, H, L, ptr, ptr))
+def least(n_in, H, L, B):
+    # two vectors' buffers, 2,048 samples per partial row, column sums, the loss's partial sums
+    al = lambda b: (b + 255) // 256 * 256
+    w, S = max(H, n_in), min(max(B // 2048, 1), 64)
+    return (2 * al(2 * B * w) + al(4 * S * w * w) + al(4 * w * (-(-B // 256))) + al(8192),
+            al(2 * B * n_in) + 2 * al(2 * B * H))
+"""
+
+
+def test_mlp_workspace_never_shrinks_with_the_batch(fake_hip):
+    """A workspace for the largest batch serves every smaller one."""
+    out = run(fake_hip, MLP + """
+Bs = sorted({b + d for b in (1, 64, 128, 256, 2048, 4096, 10240, 12288, 65536, 131072, 1 << 20)
+             for d in (-1, 0, 1, 64, 65) if b + d > 0})
+print(json.dumps([[lib.pdmp_mlp_workspace_size(mlp(n, H, L), B) for B in Bs]
+                  for n in (1, 7, 16) for H in (1, 9, 32, 100, 128, 256, 288, 512, 600, 1024)
+                  for L in (1, 3, 6)]))
+""")
+    for sizes in out:
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), sizes
+
+
+def test_mlp_workspace_of_two_buffers_is_enough(fake_hip):
+    """The inference forward, the backward and the amortised morph in a workspace of two layers'
+    activations or vectors; one byte less than the least is refused."""
+    out = run(fake_hip, MLP + """
+res = []
+for n, H, L in ((7, 16, 1), (7, 32, 3), (16, 33, 2), (6, 64, 6), (7, 100, 3), (7, 256, 3), (7, 300, 2), (5, 512, 6),
+                (7, 1001, 2), (7, 1024, 6)):
+    for B in (1, 31, 64, 127, 129, 700, 4095, 4096, 4097, 10001, 65535, 65536, 300007):
+        m = mlp(n, H, L)
+        bwd, fwd = least(n, H, L, B)
+        arm = _lib.pdmp_arm()
+        arm.n_dof, arm.pts_per_link = n, 8
+        calls = [("pdmp_mlp_forward", m, ptr, B, ptr, None, ptr, fwd, None),
+                 ("pdmp_mlp_backward", m, ptr, ptr, B, ptr, ptr, ptr, ptr, bwd, None),
+                 ("pdmp_mlp_backward_weighted", m, ptr, ptr, B, ptr, 2.0, ptr, ptr, ptr, ptr, bwd, None)]
+        if n <= 8:
+            am = lib.pdmp_amortised_workspace_size(m, C.byref(arm), B)
+            al = lambda b: (b + 255) // 256 * 256
+            am -= 2 * (al(2 * B * ((H + 7) // 8 * 8)) - al(2 * B * H))
+            q = C.c_void_p(2 << 20)
+            calls.append(("pdmp_amortised_morph", m, occ(3, 4096, (16, 16, 16)), C.byref(arm), ptr, q, B, 5, 0.1,
+                          0.5, None, None, ptr, am, None))
+        for c in calls:
+            fake.fake_launches()
+            st = getattr(lib, c[0])(*c[1:])
+            res.append((c[0], n, H, L, B, st, len(fake.fake_launches())))
+print(json.dumps(res))
+""")
+    for r in out:
+        assert r[5] == 0 and r[6] > 0, r
+
+
+def test_mlp_weight_gradient_sums_at_most_2048_samples_in_fp32(fake_hip):
+    """A partial row of a weight gradient is one FP32 accumulator's sum: of 2,048 samples, as far as
+    64 rows go, whatever the width and depth."""
+    cases = [(H, L, B) for H, L in ((64, 1), (256, 3), (256, 6), (300, 6), (512, 2), (1024, 6))
+             for B in (65536, 131072, 1 << 20)]
+    out = run(fake_hip, MLP + f"""
+print(json.dumps([launches("pdmp_mlp_backward", mlp(7, H, L), ptr, ptr, B, ptr, ptr, ptr, ptr,
+                           lib.pdmp_mlp_workspace_size(mlp(7, H, L), B), None) for H, L, B in {cases}]))
+""")
+    for (H, L, B), ls in zip(cases, out):
+        widths = [7] + [H] * L + [7]
+        tiles = [-(-a // 128) * -(-b // 128) for a, b in zip(widths, widths[1:])]
+        wg = [l["grid"][0] for l, k in zip(ls, names(ls)) if k == "k_mlp_wgrad"]
+        if len(wg) == 1:
+            tiles = [sum(tiles)]
+        for blocks, t in zip(wg, reversed(tiles)):
+            assert blocks // t >= min(64, B // 2048), (H, L, B, blocks, t)
+
+
 def test_layered_products_keep_their_waves():
     """The tiled GEMM of the widths without a fused kernel lives off eight waves per SIMD: at
     most 64 registers (5 waves: 20 to 30 % slower forwards from 65,536 samples on)."""
