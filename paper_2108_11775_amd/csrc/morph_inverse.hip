@@ -101,7 +101,8 @@ __device__ __forceinline__ void g2i_operands_h(const float *gxs, float xs, float
 // Sums at the prescaled point (xs, ys): s' (without beta), (sx, sy) with
 // grad s = -gscale (sx, sy), and with HESS (sxx, sxy, syy) with
 // Hs = gscale^2 [[sxx, sxy], [sxy, syy]] - (1/l^2) s' I, on the block's split scheme.
-template <int TB, int KS, bool HESS, bool F16>
+// APART: the FP16 k-steps are not scheduled into each other.
+template <int TB, int KS, bool HESS, bool F16, bool APART>
 __device__ __forceinline__ void g2i_eval(const uint4 *fraw, const SplitScheme &sc,
                                          const float *gxs, const float *gys, int pair, float xs,
                                          float ys, float &s, float &sx, float &sy, float &sxx,
@@ -132,6 +133,7 @@ __device__ __forceinline__ void g2i_eval(const uint4 *fraw, const SplitScheme &s
                 V[t] = mfma_h3(a1, a2, dc[0], dc[1], ks == 0 ? zero : V[t]);
                 if (HESS) Q[t] = mfma_h3(a1, a2, qc[0], qc[1], ks == 0 ? zero : Q[t]);
             }
+            if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
         }
     } else {
         const bf16x8_t *frag = reinterpret_cast<const bf16x8_t *>(fraw);
@@ -377,8 +379,9 @@ __device__ __forceinline__ void g2i_body(const uint4 *fraw, const SplitScheme &s
             g2i_eval_skip<TB, KS, H>(fraw, sc, fr, gxs, gys, kappa * x, kappa * y, s, sx, sy, sxx,
                                      sxy, syy);
         else
-            g2i_eval<TB, KS, H, F16>(fraw, sc, gxs, gys, pair, kappa * x, kappa * y, s, sx, sy,
-                                     sxx, sxy, syy);
+            g2i_eval<TB, KS, H, F16, TB == 1 && MODE == kLogdet>(fraw, sc, gxs, gys, pair,
+                                                                kappa * x, kappa * y, s, sx, sy,
+                                                                sxx, sxy, syy);
     };
     g2i_steps<MODE>(eval, beta, gscale, kappa, T, eta, iters, x, y, ld, rmax);
     if (half != 0 || i >= n) return;
@@ -388,8 +391,14 @@ __device__ __forceinline__ void g2i_body(const uint4 *fraw, const SplitScheme &s
     if (resid_out) resid_out[i] = rmax;
 }
 
+// One tile of y (g1 <= 32) holds three waves per SIMD with the log-determinant (its k-steps
+// kept apart: 134 registers; scheduled into each other 175, two waves) and four in the inverse
+// (128 registers; left to itself the compiler takes 129, three waves).  1,048,576 samples of a
+// 64 x 17 grid: log-determinant of 2 steps 157 -> 125 us, inverse of one step and iteration
+// 112 -> 101.
 template <int TB, int KS, int MODE>
-__global__ void __launch_bounds__(kIvBlock) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(kIvBlock)
+__attribute__((amdgpu_waves_per_eu(TB > 1 ? 2 : MODE == kLogdet ? 3 : 4)))
 k_grid2d_inv(const float *__restrict__ hinges, const float *__restrict__ weights, int g0, int g1,
              float kappa, float gscale, const float *x_in, int64_t n, int T, float eta, int iters,
              float *x_out, float *logdet_out, float *resid_out) {
