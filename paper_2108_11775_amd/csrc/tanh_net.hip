@@ -63,8 +63,14 @@ __device__ __forceinline__ float4 tn_ld4(const float *p) {
     return *reinterpret_cast<const float4 *>(p);
 }
 
-// Sum over the four lanes of a point (the same value in all four).
+// Sum over the four lanes of a point (the same value in all four), the same bits either way:
+// by row swaps, or (LDS) by the LDS's permute.
+template <bool LDS = false>
 __device__ __forceinline__ float tn_sum4(float p) {
+    if (LDS) {
+        p = p + __shfl_xor(p, 16, 64);
+        return p + __shfl_xor(p, 32, 64);
+    }
     auto add = [](float a, float b) { return a + b; };
     return join32(join16(p, add), add);
 }
@@ -378,7 +384,9 @@ __device__ __forceinline__ void tn_point_x6(const TnLdsX6<DIM, NT, L> &S, const 
         p = fmaf(vv.z, a[t][2], p);
         p = fmaf(vv.w, a[t][3], p);
     }
-    s = tn_sum4(p) + S.bo;
+    // one hidden layer has no products to wait for: its waves are bound by the vector unit,
+    // and the LDS is free for the sums (200,000 points, H = 5, 10 steps: 25.4 us, by swaps 27)
+    s = tn_sum4<L == 1>(p) + S.bo;
     if (!GRAD) return;
     // reverse order: e_L = v * d_L, e_l = d_l * (W_l^T e_{l+1}), grad s = W_0^T e_1
     f32x4_tn e[NT];
@@ -420,7 +428,7 @@ __device__ __forceinline__ void tn_point_x6(const TnLdsX6<DIM, NT, L> &S, const 
             q = fmaf(w.z, e[t][2], q);
             q = fmaf(w.w, e[t][3], q);
         }
-        g[k] = tn_sum4(q);
+        g[k] = tn_sum4<L == 1>(q);
     }
 }
 

@@ -253,3 +253,26 @@ def test_2d_inverse_kernels_keep_their_waves(mode, most):
     four in the inverse (5); a wave less cost 10 to 28 % from 131,072 samples on."""
     regs = kernel_registers(r"k_grid2d_invILi1ELi[1-4]ELi%dE" % mode)
     assert len(regs) == 4 and max(regs.values()) <= most, regs
+
+
+def test_tanh_net_of_one_hidden_layer_sums_in_the_lds(tmp_path):
+    """No products to wait for: the lanes' sums by row swaps, on the busy vector unit, cost 3 to
+    6 % from 33,000 points on."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    from paper_2108_11775_amd import _lib
+    data = open(_lib.LIB_PATH, "rb").read()
+    seen, name, at = {}, "", data.find(b"\x7fELF", 1)
+    while at >= 0:
+        if data[at + 18:at + 20] == b"\xe0\x00":  # EM_AMDGPU
+            (tmp_path / "co").write_bytes(data[at:])
+            r = subprocess.run([objdump, "-d", str(tmp_path / "co")], capture_output=True)
+            for line in r.stdout.decode(errors="replace").splitlines():
+                m = re.match(r"[0-9a-f]+ <(.*)>:", line)
+                name = m[1] if m else name
+                if "k_tanh_netILi" in name and ("_bpermute" in line or "v_permlane" in line):
+                    seen.setdefault(name, set()).add("swap" if "v_permlane" in line else "lds")
+        at = data.find(b"\x7fELF", at + 4)
+    one = {k: v for k, v in seen.items() if re.search(r"ILi[23]ELi[124]ELi1E", k)}
+    assert len(one) == 18 and all(v == {"lds"} for v in one.values()), one
