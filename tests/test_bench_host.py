@@ -4,6 +4,7 @@ helpers; the GPU tests hold the library's own report to it) and bench.py's comma
 line refusals."""
 import math
 import os
+import re
 import subprocess
 import sys
 
@@ -71,3 +72,18 @@ def test_cli_refusals():
     r = _run("--workloads", "arm,nonsense")
     assert r.returncode != 0 and "nonsense" in r.stderr
 
+
+
+def test_counters_are_keyed_to_every_source_of_the_kernel():
+    """The counted figures are reported for one state of grid2d.hip and all of csrc it includes."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2108_11775_amd", "csrc")
+    seen, todo = set(), ["grid2d.hip"]
+    while todo:
+        f = todo.pop()
+        if f in seen or not os.path.exists(os.path.join(csrc, f)):
+            continue
+        seen.add(f)
+        with open(os.path.join(csrc, f)) as fh:
+            todo += re.findall(r'^#include "([^"]+)"', fh.read(), re.M)
+    assert set(bench.GRID2D_SOURCES) == seen and len(bench.GRID2D_SOURCES) == len(seen)
