@@ -71,9 +71,9 @@ typedef enum {
  *           BF16 splits otherwise; the pairwise sum where that is as fast, and on 3-D
  *           grids below 16^3 for weights that are not finite or that neither split
  *           carries (above 2^80, nonzero below 2^-100).
- *           Every call that takes the factorised path first checks the statement
- *           on the device (each hinge equal, by value, to its axis coordinates; a
- *           NaN coordinate fails).  Hinges that are not that grid give undefined
+ *           Every call that takes the factorised path checks the statement on the
+ *           device, before its work or beside it (each hinge equal, by value, to its
+ *           axis coordinates; a NaN coordinate fails).  Hinges that are not that grid give undefined
  *           results of that call, which still runs to completion, and the next
  *           pdmp_sync() returns PDMP_EINVAL (the flag is per device and cleared by
  *           that report).

@@ -2,8 +2,8 @@
 //
 // An occupancy whose `grid` field is set is evaluated through the per-axis
 // factorisation, which reads only the axis entries of the hinge array (X0[i] = h[i],
-// X1[i] = h[M + g0 i], X2[i] = h[2M + g0 g1 i]).  Before such a launch the entry
-// points enqueue this check on the same stream: every hinge j = i0 + g0 (i1 + g1 i2)
+// X1[i] = h[M + g0 i], X2[i] = h[2M + g0 g1 i]).  With such a launch the entry
+// points enqueue this check on the same stream, before it or inside it: every hinge j = i0 + g0 (i1 + g1 i2)
 // must equal (X0[i0], X1[i1], X2[i2]) (by value; a NaN coordinate fails).  A mismatch
 // sets a sticky per-device word that pdmp_sync reports as PDMP_EINVAL and clears;
 // the launch itself runs to completion (its results are then undefined).

@@ -321,9 +321,9 @@ k_sum_splits(const float *__restrict__ part, int S, int64_t MN, float *out,
 // contraction index in its natural order, so that every Z is the layered path's bits: a
 // lane's two quads of a 16-column block lie 8 columns apart, and one v_permlane32_swap
 // per register exchanges them with the other half's into 8 consecutive columns (the operand
-// and a 16-byte store).  HBM writes bound it: 288 MB at 65,536 x 256 x 3.  Samples past the
+// and a 16-byte store).  HBM writes bound it: 302 MB at 65,536 x 256 x 3.  Samples past the
 // batch repeat the last one and store into the arrays' padding (whole blocks of 128).
-// At 65,536 x (7-256-256-256-7): 66 us; one GEMM per layer took 120 us.
+// At 65,536 x (7-256-256-256-7): 68 us; one GEMM per layer took 120 us.
 constexpr int kMlpFB = 256;  // 4 waves, 128 samples; two blocks per CU
 
 // Slot of column x (0..15) of a 16-column block in the A fragments: lane half h reads
@@ -544,8 +544,8 @@ __device__ __forceinline__ bf16x8_t tr_frag(const uint16_t *T, int k0, TrOff o) 
 // accumulator layout as k_mlp_fused (C = W^T dZ^T, a wave its own 32 samples), the
 // contraction in natural order as its training form; W_l is staged row-major in passes of
 // TP column tiles and read transposed.  The vectors go from layer to layer in registers;
-// each is stored once for the weight gradients.  HBM bound: Z read, dZ written (288 MB at
-// 65,536 x 256 x 3), where one GEMM per layer also read every dZ back: 61 us against 160 us.
+// each is stored once for the weight gradients.  HBM bound: Z read, dZ written (302 MB at
+// 65,536 x 256 x 3), where one GEMM per layer also read every dZ back: 64 us against 160 us.
 struct MlpChain {
     const float *z[kMlpMaxHidden];
     uint16_t *dz[kMlpMaxHidden];
@@ -670,7 +670,7 @@ k_mlp_chain(const uint16_t *__restrict__ wbf, int n_in, int L, const uint16_t *d
 // loads in flight during a round's products, two buffers) and read transposed.  Four waves own
 // 64 x 64 outputs each.  The bias sums come from the dZ rows as they are staged (FP32 over
 // a thread's two rows of a round, FP64 across rounds and threads, fixed order).
-// At 65,536 x (7-256-256-256-7): 70 us, 205 MB read and 22 MB written (46 us at the rate of a
+// At 65,536 x (7-256-256-256-7): 67 us, 205 MB read and 22 MB written (46 us at the rate of a
 // plain copy); one GEMM per layer with 2-byte transposing stores, the row sums and the column
 // sums took 370 us.  A round's LDS traffic and barrier bind it, not HBM.
 constexpr int kWgSamples = 256, kWgSlots = 512;  // samples per partial row; blocks at once

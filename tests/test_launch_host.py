@@ -158,7 +158,7 @@ print(json.dumps([[lib.pdmp_mlp_workspace_size(mlp(n, H, L), B) for B in Bs]
 
 def test_mlp_workspace_of_two_buffers_is_enough(fake_hip):
     """The inference forward, the backward and the amortised morph in a workspace of two layers'
-    activations or vectors; one byte less than the least is refused."""
+    activations or vectors."""
     out = run(fake_hip, MLP + """
 res = []
 for n, H, L in ((7, 16, 1), (7, 32, 3), (16, 33, 2), (6, 64, 6), (7, 100, 3), (7, 256, 3), (7, 300, 2), (5, 512, 6),
