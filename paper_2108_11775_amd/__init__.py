@@ -42,11 +42,11 @@ def _torch():
 
 
 def _stream(device=None):
-    """The current stream's handle on `device` (default the current device)."""
+    """The current stream's handle on `device`, as torch names one (default the current device)."""
     torch = _torch()
-    # the handle itself: building torch's Stream object first costs 2 us, a tenth of a
-    # small call
-    if device is not None and device.type == "cuda" and device.index is not None:
+    # a tensor's device: the handle itself, as building torch's Stream object first costs
+    # 2 us, a tenth of a small call
+    if isinstance(device, torch.device) and device.type == "cuda" and device.index is not None:
         return torch._C._cuda_getCurrentRawStream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 

@@ -276,3 +276,18 @@ def test_tanh_net_of_one_hidden_layer_sums_in_the_lds(tmp_path):
         at = data.find(b"\x7fELF", at + 4)
     one = {k: v for k, v in seen.items() if re.search(r"ILi[23]ELi[124]ELi1E", k)}
     assert len(one) == 18 and all(v == {"lds"} for v in one.values()), one
+
+
+@pytest.mark.parametrize("device", [None, 1, "cuda:1", "cuda"])
+def test_sync_takes_a_device_as_torch_names_it(monkeypatch, device):
+    import types
+
+    import torch
+
+    import paper_2108_11775_amd as P
+    seen = []
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda d=None: types.SimpleNamespace(cuda_stream=("stream of", d)))
+    monkeypatch.setattr(P._lib, "call", lambda *a: seen.append(a))
+    P.sync(device)
+    assert seen == [("pdmp_sync", ("stream of", device))]
