@@ -175,21 +175,25 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
     }
 
     const int n = n0 + wn * 32 + (lane & 31);
+    // one product of the lane's row with each row length; the 16 rows are uniform steps from it
+    // (65,536 x 7-288-7 forward 45.2 -> 44.2 us)
+    const int mb = m0 + wm * 32 + 4 * (lane >> 5);
+    const int64_t cb = (int64_t)mb * g.N + n, hb = (int64_t)mb * g.ldh + n;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        const int r = 8 * (v >> 2) + (v & 3), m = mb + r;
         if (m >= g.M || n >= g.N) continue;
         const float a = acc[v];
-        const int64_t mn = (int64_t)m * g.N + n;
+        const int64_t mn = cb + (int64_t)r * g.N;
         if (EPI == kEpiHidden) {
             const float z = a + g.bias[n];
             if (g.zsave) g.zsave[mn] = z;
-            g.hout[(int64_t)m * g.ldh + n] = f32_to_bf16(silu_f(z));
+            g.hout[hb + (int64_t)r * g.ldh] = f32_to_bf16(silu_f(z));
         } else if (EPI == kEpiOut) {
             const int64_t o = (int64_t)n * g.ldq + m;  // SoA [n_out][B], m = sample
             g.qout[o] = g.qin[o] + (a + g.bias[n]);
         } else {
-            g.hout[(int64_t)m * g.ldh + n] = f32_to_bf16(a * silu_grad_f(g.zprev[mn]));
+            g.hout[hb + (int64_t)r * g.ldh] = f32_to_bf16(a * silu_grad_f(g.zprev[mn]));
         }
     }
 }
