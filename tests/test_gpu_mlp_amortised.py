@@ -524,3 +524,11 @@ def test_mse_gradient_edges_of_blocks_and_ranges(n_in, hidden, n_hidden, B):
                 a, b = grad[off:off + n_el], gref[off:off + n_el]
                 assert np.linalg.norm(a - b) <= (tol + 1e-3) * np.linalg.norm(b), (sel, fi, fo, n_el)
                 off += n_el
+
+
+@pytest.mark.parametrize("n_in,hidden,n_hidden,B", [(8, 8, 2, 1), (7, 40, 2, 63), (16, 72, 1, 65), (7, 24, 3, 129),
+                                                    (7, 1000, 2, 1), (3, 288, 3, 191)])
+def test_layered_products_at_ragged_ends(n_in, hidden, n_hidden, B):
+    """Tiles of the layered path that end within their rows or, with widths a multiple of 8, within
+    their contraction: 16-byte loads give the bits of element-wise ones (odd addresses)."""
+    test_mlp_buffers_of_any_4_byte_alignment(n_in, hidden, n_hidden, B)
