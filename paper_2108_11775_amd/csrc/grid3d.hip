@@ -648,7 +648,9 @@ __device__ __forceinline__ void arm_body(const pdmp_arm &arm, const uint4 *fraw,
         }
         wave_lds_sync();
         float SG[3] = {0, 0, 0}, SM[3] = {0, 0, 0};
-#pragma unroll 1
+        // the check's links two at a time: one link's tables beside the other's products (4,000
+        // configurations: 2 links 10.4 -> 9.9 us, 7 17.0 -> 15.3; a morph's, 3 % slower)
+#pragma unroll(MORPH ? 1 : 2)
         for (int l = NDOF - 1; l >= 0; --l) {
             float p[3], ol[3];
 #pragma unroll
@@ -906,12 +908,13 @@ static bool g3_ws_pays(int mode, const G3Dims &g, int64_t n, int T) {
 // 16^3 hinges, 1 to 16,000 configurations (us): k_arm_grid3d 8 + T (0.6 + 1.9 n_dof); wide 8 +
 // 4 (r - 1) + T (0.2 + 4 r) in r rounds, of up to 4 links 8 + 2 (r - 1) + T (1.3 + 1.4 r).
 // (10 steps, 7 links: 1,000 configurations 53 against 146, 2,000 95 / 146, 3,000 138 / 147,
-// 4,000 181 / 152; one step of 3,000: 28 / 23.  One link: 37 / 32 at any size.)  The check: 10,
-// 13, 17 us in 1, 2, 3 rounds against 7.9 + 1.3 n_dof (padded grids, two links: 10.4 / 9.4).
+// 4,000 181 / 152; one step of 3,000: 28 / 23.  One link: 37 / 32 at any size.)  The check: 9.2
+// to 10, 11.2 to 13, 17 us in 1, 2, 3 rounds against 7.9 + 1.1 n_dof (4 links 13.0, 8 18.2;
+// padded grids, two links: 10.4 / 9.4).
 static bool arm_wide_pays(int n_dof, bool full, bool morph, int64_t n, int T) {
     if (n_dof < 2 || n > 3072) return false;
     const int r = (int)((n + 1023) / 1024);
-    if (!morph) return 5 * r <= 2 * n_dof + (full ? 2 : 0);
+    if (!morph) return full ? n_dof >= 1 << r : 5 * r <= 2 * n_dof;
     return n_dof > 4 ? T * (0.4 + 1.9 * n_dof - 4 * r) >= 4 * (r - 1)
                      : T * (1.9 * n_dof - 0.7 - 1.4 * r) >= 2 * (r - 1);
 }
